@@ -15,14 +15,15 @@ using namespace gorila;
 namespace {
 // Stages of the calls, in launch order (bits of the timing mask).  The
 // minibatch resolution (or a forward call's frame table) shares the prep
-// launch.
+// launch; conv_fwd is conv1 to conv3 in one launch, where a call runs them so.
 enum Stage {
     ST_PREP, ST_CONV1_FWD, ST_CONV2_FWD, ST_CONV3_FWD, ST_FC1_FWD, ST_HEAD,
-    ST_FC1_BWD, ST_CONV3_BWD, ST_CONV2_BWD, ST_CONV1_WGRAD, ST_GRAD_REDUCE, ST_COUNT
+    ST_FC1_BWD, ST_CONV3_BWD, ST_CONV2_BWD, ST_CONV1_WGRAD, ST_GRAD_REDUCE, ST_CONV_FWD, ST_COUNT
 };
 const char* const STAGE_NAMES[ST_COUNT] = {
     "prep_weights", "conv1_fwd", "conv2_fwd", "conv3_fwd", "fc1_fwd", "head",
-    "fc1_bwd", "conv3_bwd", "conv2_bwd", "conv1_wgrad", "grad_reduce"};
+    "fc1_bwd", "conv3_bwd", "conv2_bwd", "conv1_wgrad", "grad_reduce",
+    "conv_fwd"};
 struct TimingRecord {
     int stage;
     hipEvent_t start, stop;
@@ -74,11 +75,14 @@ constexpr size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 // Byte offsets of every workspace region for fwd_rows forward rows (all
 // parameter sets together), bwd_rows learner rows, `online` learner parameter
 // sets plus one target set, and `widened` fp32 copies of bf16 parameter sets.
+constexpr int FRAG_PLANES = 3;  // room for fp32 weights
 constexpr size_t W2T_BYTES = 4 * 16 * 64 * 32, W3T_BYTES = 4 * 9 * 64 * 64;
 struct Plan {
     size_t err, zero, ftab, a, r, term;
     size_t theta32, theta32_stride;
-    size_t w2t, w3t, w3d, w2p;  // bases of per-set arrays (stride W2T_BYTES / W3T_BYTES)
+    size_t frag;
+    // bases of per-set arrays (stride W2T_BYTES or W3T_BYTES)
+    size_t w2t, w3t, w3d, w2p;
     size_t h1, h2, h3, h4, q, ell, coef, td;
     size_t dz4, dz3, dz2, dz1;
     size_t fc1part, part1, part2, part3, bpart, hpart;
@@ -109,12 +113,14 @@ constexpr Plan make_plan(int64_t fwd_rows, int64_t bwd_rows, int A, int online =
     p.term = take((size_t)B);
     p.theta32_stride = up(4 * (size_t)param_count(A));
     p.theta32 = take(p.theta32_stride * (size_t)widened);
-    p.w2t = take(W2T_BYTES * (size_t)(online + 1));
-    p.w3t = take(W3T_BYTES * (size_t)(online + 1));
+    p.frag = B ? o : take(FRAG_PLANES * FRAG_BYTES);  // forward-only calls
+    p.w2t = B ? take(W2T_BYTES * (size_t)(online + 1)) : o;
+    p.w3t = B ? take(W3T_BYTES * (size_t)(online + 1)) : o;
     p.w3d = take(W3T_BYTES * (size_t)online);
     p.w2p = take(W2T_BYTES * (size_t)online);
-    p.h1 = take(4 * (size_t)F * P1 * C1);
-    p.h2 = take(4 * (size_t)F * P2 * C2);
+    // forward-only calls keep h1 and h2 in LDS
+    p.h1 = B ? take(4 * (size_t)F * P1 * C1) : o;
+    p.h2 = B ? take(4 * (size_t)F * P2 * C2) : o;
     p.h3 = take(4 * (size_t)F * FLAT);
     p.h4 = take(4 * (size_t)F * HID);
     p.q = take(4 * (size_t)F * A);
@@ -131,7 +137,7 @@ constexpr Plan make_plan(int64_t fwd_rows, int64_t bwd_rows, int A, int online =
     p.part3 = B ? take(4 * (size_t)WG_MAX_SPLITS * C3 * 9 * C2) : o;
     p.bpart = B ? take(4 * (size_t)3 * BIAS_PART_STRIDE) : o;
     p.hpart = B ? take(4 * (size_t)online * HEAD_MAX_BLOCKS * HP_STRIDE) : o;
-    p.split = take(4 * (size_t)SPLIT_MAX_SLOTS * SPLIT_TILE_FLOATS);
+    p.split = B ? take(4 * (size_t)SPLIT_MAX_SLOTS * SPLIT_TILE_FLOATS) : o;
     p.total = o;
     return p;
 }
@@ -139,16 +145,14 @@ constexpr Plan make_plan(int64_t fwd_rows, int64_t bwd_rows, int A, int online =
 template <class T>
 T* at(gorila_ctx* c, size_t off) { return (T*)(c->ws + off); }
 
-// Split-reduction workspace of a plan laid out from `base` (the context's
-// workspace, or the no-allocation scratch).
-SplitWs split_ws(gorila_ctx* c, char* base, const Plan& p) {
+// Split-reduction workspace of a plan.
+SplitWs split_ws(gorila_ctx* c, const Plan& p) {
     SplitWs sw;
     sw.cus = c->cus;
-    sw.ws = c->split_ok ? (float*)(base + p.split) : nullptr;  // null: every tile whole
-    sw.cnt = (int*)(base + p.err + SPLIT_CNT_OFFSET);
+    sw.ws = c->split_ok ? (float*)(c->ws + p.split) : nullptr;  // null: every tile whole
+    sw.cnt = (int*)(c->ws + p.err + SPLIT_CNT_OFFSET);
     return sw;
 }
-SplitWs split_ws(gorila_ctx* c, const Plan& p) { return split_ws(c, c->ws, p); }
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
@@ -214,8 +218,7 @@ ReplayView view_of(const gorila_replay* rv) {
 // the rest widen a bf16 set (independent, so one launch).
 __global__ __launch_bounds__(256) void states_prep_kernel(const uint8_t* states, int n,
                                                           const uint8_t** ftab, WeightViews wv,
-                                                          int tblocks, unsigned* zero_head,
-                                                          WidenJob wj, int wpn) {
+                                                          int tblocks, WidenJob wj, int wpn) {
     if ((int)blockIdx.x >= tblocks + PREP_BLOCKS) {
         widen_part(wj, 0, blockIdx.x - tblocks - PREP_BLOCKS, wpn);
         return;
@@ -224,20 +227,15 @@ __global__ __launch_bounds__(256) void states_prep_kernel(const uint8_t* states,
         prep_weights_part(wv, blockIdx.x - tblocks, PREP_BLOCKS);
         return;
     }
-    // a scratch that other calls share starts each call with a zero head
-    // (error word, split-reduction counters); the split launches come later
-    if (zero_head && blockIdx.x == 0)
-        for (int i = threadIdx.x; i < (int)(WS_HEAD / 4); i += blockDim.x) zero_head[i] = 0u;
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e < n * 4) ftab[e] = states + (int64_t)(e >> 2) * STATE_BYTES + (int64_t)(e & 3) * FRAME_BYTES;
 }
 
 // Forward pass of n states through one parameter set up to h4, with the
 // plan's regions laid out from `base`; *theta32 receives the fp32 parameters
-// the head must use.  zero_head: clear the plan's head first.
+// the head must use.
 int forward_one(gorila_ctx* c, char* base, const Plan& p, const gorila_params* prm,
-                const uint8_t* states, int n, const float** theta32, int* fc1_splits,
-                bool zero_head) {
+                const uint8_t* states, int n, const float** theta32, int* fc1_splits) {
     hipStream_t st = c->stream;
     auto fp = [&](size_t off) { return (float*)(base + off); };
     const uint8_t** ftab = (const uint8_t**)(base + p.ftab);
@@ -251,24 +249,23 @@ int forward_one(gorila_ctx* c, char* base, const Plan& p, const gorila_params* p
         theta = wj.set.dst[0];
     }
     *theta32 = theta;
-    WeightViews wv{theta, fp(p.w2t), fp(p.w3t), nullptr, nullptr};
+    WeightViews wv{theta};
+    wv.frag = (uint16_t*)(base + p.frag);
+    wv.planes = wj.n ? 1 : 3;
     if (wj.n) wv.theta16 = wj.set.src[0];
     {
         StageTimer t(c, ST_PREP);
         const int tblocks = (n * 4 + 255) / 256, wpn = wj.blocks_per_net();
         states_prep_kernel<<<tblocks + PREP_BLOCKS + wpn, 256, 0, st>>>(
-            states, n, ftab, wv, tblocks, zero_head ? (unsigned*)(base + p.err) : nullptr, wj,
-            wpn > 0 ? wpn : 1);
+            states, n, ftab, wv, tblocks, wj, wpn > 0 ? wpn : 1);
     }
-    GroupPtrs th{}, w2t{}, w3t{};
+    GroupPtrs th{};
     th.p[0] = theta;
-    w2t.p[0] = wv.w2t;
-    w3t.p[0] = wv.w3t;
-    // forward-only calls compute in fp32 (bf16 parameters are widened exactly)
-    { StageTimer t(c, ST_CONV1_FWD); launch_conv1_fwd(ftab, th, 1, n, fp(p.h1), false, st); }
-    const SplitWs sw = split_ws(c, base, p);
-    { StageTimer t(c, ST_CONV2_FWD); launch_conv2_fwd(fp(p.h1), w2t, th, 1, n, fp(p.h2), sw, false, st); }
-    { StageTimer t(c, ST_CONV3_FWD); launch_conv3_fwd(fp(p.h2), w3t, th, 1, n, fp(p.h3), sw, false, st); }
+    // forward-only calls compute in fp32 (bf16 parameters are exact in one plane)
+    {
+        StageTimer t(c, ST_CONV_FWD);
+        launch_trunk_fwd(ftab, wv.frag, wv.planes, theta, n, fp(p.h3), c->cus, st);
+    }
     { StageTimer t(c, ST_FC1_FWD); *fc1_splits = launch_fc1_fwd(fp(p.h3), th, GroupPtrs16{}, 1, n, fp(p.fc1part), false, st); }
     return check_launch();
 }
@@ -510,7 +507,7 @@ int gorila_q_forward(const gorila_params* params, const uint8_t* states_u8, int3
     const float* theta = nullptr;
     int splits = 0;
     ctx->td_valid = false;  // the forward rows overwrite a learner call's q
-    if ((rc = forward_one(ctx, ctx->ws, p, params, states_u8, n, &theta, &splits, false))) return rc;
+    if ((rc = forward_one(ctx, ctx->ws, p, params, states_u8, n, &theta, &splits))) return rc;
     {
         StageTimer t(ctx, ST_HEAD);
         launch_q_head(at<float>(ctx, p.fc1part), splits, theta, n, params->n_actions, q_out,
@@ -532,7 +529,7 @@ int gorila_act(const gorila_params* params, const uint8_t* states_u8, int32_t n,
     const float* theta = nullptr;
     int splits = 0;
     ctx->td_valid = false;  // the forward rows overwrite a learner call's q
-    if ((rc = forward_one(ctx, ctx->ws, p, params, states_u8, n, &theta, &splits, false))) return rc;
+    if ((rc = forward_one(ctx, ctx->ws, p, params, states_u8, n, &theta, &splits))) return rc;
     {
         StageTimer t(ctx, ST_HEAD);
         launch_act_head(at<float>(ctx, p.fc1part), splits, theta, n, params->n_actions, eps, seed,
@@ -556,7 +553,7 @@ int gorila_act_noalloc(const gorila_params* params, const uint8_t* states_u8, in
     if (p.total > NOALLOC_PROBE) return GORILA_EWORKSPACE;  // cannot happen: the plan grows with n, A
     const float* theta = nullptr;
     int splits = 0;
-    if ((rc = forward_one(ctx, ctx->scratch, p, params, states_u8, n, &theta, &splits, true)))
+    if ((rc = forward_one(ctx, ctx->scratch, p, params, states_u8, n, &theta, &splits)))
         return rc;
     {
         StageTimer t(ctx, ST_HEAD);
@@ -660,8 +657,8 @@ int learner_steps(gorila_ctx* ctx, const gorila_params* params, int G, bool allo
     float* h3 = at<float>(ctx, p.h3);
     float* h4 = at<float>(ctx, p.h4);
     float* fc1part = at<float>(ctx, p.fc1part);
-    { StageTimer t(ctx, ST_CONV1_FWD); launch_conv1_fwd(ftab, th, 2 * G, b, h1, bf16, st); }
     const SplitWs sw = split_ws(ctx, p);
+    { StageTimer t(ctx, ST_CONV1_FWD); launch_conv1_fwd(ftab, th, 2 * G, b, h1, bf16, st); }
     { StageTimer t(ctx, ST_CONV2_FWD); launch_conv2_fwd(h1, w2t, th, 2 * G, b, h2, sw, bf16, st); }
     { StageTimer t(ctx, ST_CONV3_FWD); launch_conv3_fwd(h2, w3t, th, 2 * G, b, h3, sw, bf16, st); }
     int S = 0;

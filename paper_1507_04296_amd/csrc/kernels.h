@@ -39,19 +39,22 @@ void launch_insert(uint8_t* frames, uint8_t* ep_start, int32_t* action, float* r
                    const uint8_t* ep_in, const int32_t* act_in, const float* rew_in, int records,
                    hipStream_t st);
 
-// Transposed conv weights used as MFMA operands.
+// Conv weights as the kernels read them.  Each may be null (not wanted).
+//  frag: the forward operands of trunk.hip, `planes` bf16 planes each (below)
 //  w2t [16][64][32]: W2[o][c][u][v] at [(u,v)][o][c]   (conv2 forward)
 //  w3t [9][64][64]:  W3[o][c][u][v] at [(u,v)][o][c]   (conv3 forward)
 //  w3d [9][64][64]:  W3[o][c][u][v] at [(u,v)][c][o]   (conv3 data gradient)
 //  w2p [4][4][32][64]: W2[o][c][u][v] at [(u/2,v/2)][(u%2,v%2)][c][o]  (conv2 data gradient)
 struct WeightViews {
     const float* theta;   // flat parameters
-    float* w2t;
-    float* w3t;
-    float* w3d;           // may be null (forward only)
-    float* w2p;           // may be null
+    uint16_t* frag = nullptr;
+    int planes = 0;       // 3 for fp32 weights, 1 for bf16 ones
+    float* w2t = nullptr;
+    float* w3t = nullptr;
+    float* w3d = nullptr;
+    float* w2p = nullptr;
     // when not null: the same parameters as bf16 bit patterns, which the
-    // transposes read (and widen exactly) instead of theta, so that they need
+    // packing reads (and widens exactly) instead of theta, so that it need
     // not wait for theta's widened copy
     const uint16_t* theta16 = nullptr;
 };
@@ -60,38 +63,75 @@ struct WeightViewSet {
     WeightViews v[MAX_NETS];
 };
 
-// Block `blk` of `nblk` (256 threads each) of one net's transposes.  Every
+// Forward operand fragments: fragment f is one 16 x 32 operand of
+// v_mfma_f32_16x16x32_bf16 (16 output channels, 32 reduction indices) in lane
+// order, 16 bytes a lane: lane l holds channel l % 16 and indices 8 (l / 16)
+// .. +7.  Planes of one fragment follow one another:
+// frag[((f * planes + plane) * 64 + lane) * 8].
+//   conv1: f = FRAG1 + 2 * step + channel tile; 8 steps of 32 in OIHW order
+//   conv2: f = FRAG2 + 4 * tap + channel tile; 32 input channels
+//   conv3: f = FRAG3 + 4 * (2 * tap + input channel half) + channel tile
+constexpr int FRAG1 = 0, FRAG2 = 16, FRAG3 = 80, NFRAG = 152;
+constexpr size_t FRAG_BYTES = (size_t)NFRAG * 1024;  // per plane
+
+// Block `blk` of `nblk` (256 threads each) of one net's packing.  Every
 // destination is written in index order (coalesced); the scattered reads come
-// from the 128 KB of W2 and W3, which stay in L2.
+// from the 300 KB of W1, W2 and W3, which stay in L2.
 constexpr int PREP_BLOCKS = 64;  // blocks per net
 __device__ inline void prep_weights_part(const WeightViews& v, int blk, int nblk) {
     // W2 [o][c][u][v], 64 x 32 x 4 x 4; W3 [o][c][u][v], 64 x 64 x 3 x 3
-    auto W2 = [&](int i) {
-        return v.theta16 ? __uint_as_float((uint32_t)v.theta16[OFF_W2 + i] << 16) : v.theta[OFF_W2 + i];
-    };
-    auto W3 = [&](int i) {
-        return v.theta16 ? __uint_as_float((uint32_t)v.theta16[OFF_W3 + i] << 16) : v.theta[OFF_W3 + i];
+    auto W = [&](int64_t i) {
+        return v.theta16 ? __uint_as_float((uint32_t)v.theta16[i] << 16) : v.theta[i];
     };
     const int stride = nblk * 256;
+    for (int d = blk * 256 + (int)threadIdx.x; v.frag && d < NFRAG * 64; d += stride) {
+        const int f = d >> 6, l = d & 63, q = l >> 4, o16 = l & 15;
+        int64_t at;
+        int step;  // distance between a lane's eight values
+        if (f < FRAG2) {
+            at = OFF_W1 + ((f & 1) * 16 + o16) * 256 + (f >> 1) * 32 + 8 * q;
+            step = 1;
+        } else if (f < FRAG3) {
+            const int t = (f - FRAG2) >> 2, o = (f & 3) * 16 + o16;
+            at = OFF_W2 + (o * 32 + 8 * q) * 16 + t;
+            step = 16;
+        } else {
+            const int s = (f - FRAG3) >> 2, o = (f & 3) * 16 + o16;
+            at = OFF_W3 + (o * 64 + (s & 1) * 32 + 8 * q) * 9 + (s >> 1);
+            step = 9;
+        }
+        float w[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[e] = W(at + e * step);
+        for (int pl = 0; pl < v.planes; ++pl) {
+            bf16x8 b;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                b[e] = (__bf16)w[e];
+                w[e] -= (float)b[e];  // exact
+            }
+            *(bf16x8*)(v.frag + ((size_t)(f * v.planes + pl) * 64 + l) * 8) = b;
+        }
+    }
     for (int d = blk * 256 + (int)threadIdx.x; d < 16 * 64 * 32; d += stride) {
-        {  // w2t[t][o][c], t = u*4 + v
+        if (v.w2t) {  // w2t[t][o][c], t = u*4 + v
             const int c = d & 31, o = (d >> 5) & 63, t = d >> 11;
-            v.w2t[d] = W2(((o * 32 + c) * 4 + (t >> 2)) * 4 + (t & 3));
+            v.w2t[d] = W(OFF_W2 + (o * 32 + c) * 16 + t);
         }
         if (v.w2p) {  // w2p[tp][phase][c][o]: tap pair (u/2, v/2), stride phase (u%2, v%2)
             const int o = d & 63, c = (d >> 6) & 31, phase = (d >> 11) & 3, tp = d >> 13;
             const int u = (tp >> 1) * 2 + (phase >> 1), vv = (tp & 1) * 2 + (phase & 1);
-            v.w2p[d] = W2(((o * 32 + c) * 4 + u) * 4 + vv);
+            v.w2p[d] = W(OFF_W2 + ((o * 32 + c) * 4 + u) * 4 + vv);
         }
     }
     for (int d = blk * 256 + (int)threadIdx.x; d < 9 * 64 * 64; d += stride) {
-        {  // w3t[t][o][c], t = u*3 + v
+        if (v.w3t) {  // w3t[t][o][c], t = u*3 + v
             const int c = d & 63, o = (d >> 6) & 63, t = d >> 12;
-            v.w3t[d] = W3((o * 64 + c) * 9 + t);
+            v.w3t[d] = W(OFF_W3 + (o * 64 + c) * 9 + t);
         }
         if (v.w3d) {  // w3d[t][c][o]
             const int o = d & 63, c = (d >> 6) & 63, t = d >> 12;
-            v.w3d[d] = W3((o * 64 + c) * 9 + t);
+            v.w3d[d] = W(OFF_W3 + (o * 64 + c) * 9 + t);
         }
     }
 }
@@ -154,6 +194,11 @@ void launch_resolve_prep(const ReplayView& rv, const int64_t* idx, int n, int n_
 // Forward layers.  `groups` parameter sets; group g owns rows [g*n, (g+1)*n)
 // of every activation buffer.  bf16: the parameter sets hold bf16 values
 // (widened to fp32) and the products run on bf16 MFMA operands (common.h).
+// Learner steps run layer by layer (their backward pass reads h1 and h2);
+// forward-only calls take conv1 to conv3 of one set in one launch (trunk.hip):
+// frag as WeightViews packed it (`planes` planes), biases from theta, h3 [n][64][49].
+void launch_trunk_fwd(const uint8_t* const* ftab, const uint16_t* frag, int planes,
+                      const float* theta, int n, float* h3, int cus, hipStream_t st);
 void launch_conv1_fwd(const uint8_t* const* ftab, const GroupPtrs& theta, int groups, int n,
                       float* h1, bool bf16, hipStream_t st);
 // Workspace for balancing a launch (TailSplit): ws holds SPLIT_MAX_SLOTS
