@@ -18,11 +18,11 @@ namespace {
 // launch; conv_fwd is conv1 to conv3 in one launch, where a call runs them so.
 enum Stage {
     ST_PREP, ST_CONV1_FWD, ST_CONV2_FWD, ST_CONV3_FWD, ST_FC1_FWD, ST_HEAD,
-    ST_FC1_BWD, ST_CONV3_BWD, ST_CONV2_BWD, ST_CONV1_WGRAD, ST_GRAD_REDUCE, ST_CONV_FWD, ST_COUNT
+    ST_FC1_BWD, ST_CONV_DGRAD, ST_CONV_WGRAD, ST_CONV1_WGRAD, ST_GRAD_REDUCE, ST_CONV_FWD, ST_COUNT
 };
 const char* const STAGE_NAMES[ST_COUNT] = {
     "prep_weights", "conv1_fwd", "conv2_fwd", "conv3_fwd", "fc1_fwd", "head",
-    "fc1_bwd", "conv3_bwd", "conv2_bwd", "conv1_wgrad", "grad_reduce",
+    "fc1_bwd", "conv_dgrad", "conv_wgrad", "conv1_wgrad", "grad_reduce",
     "conv_fwd"};
 struct TimingRecord {
     int stage;
@@ -81,8 +81,8 @@ struct Plan {
     size_t err, zero, ftab, a, r, term;
     size_t theta32, theta32_stride;
     size_t frag;
-    // bases of per-set arrays (stride W2T_BYTES or W3T_BYTES)
-    size_t w2t, w3t, w3d, w2p;
+    // bases of per-set arrays (stride W2T_BYTES, W3T_BYTES, FRAG_PLANES * FRAGD_BYTES)
+    size_t w2t, w3t, fragd;
     size_t h1, h2, h3, h4, q, ell, coef, td;
     size_t dz4, dz3, dz2, dz1;
     size_t fc1part, part1, part2, part3, bpart, hpart;
@@ -116,8 +116,7 @@ constexpr Plan make_plan(int64_t fwd_rows, int64_t bwd_rows, int A, int online =
     p.frag = B ? o : take(FRAG_PLANES * FRAG_BYTES);  // forward-only calls
     p.w2t = B ? take(W2T_BYTES * (size_t)(online + 1)) : o;
     p.w3t = B ? take(W3T_BYTES * (size_t)(online + 1)) : o;
-    p.w3d = take(W3T_BYTES * (size_t)online);
-    p.w2p = take(W2T_BYTES * (size_t)online);
+    p.fragd = B ? take(FRAG_PLANES * FRAGD_BYTES * (size_t)online) : o;
     // forward-only calls keep h1 and h2 in LDS
     p.h1 = B ? take(4 * (size_t)F * P1 * C1) : o;
     p.h2 = B ? take(4 * (size_t)F * P2 * C2) : o;
@@ -130,7 +129,7 @@ constexpr Plan make_plan(int64_t fwd_rows, int64_t bwd_rows, int A, int online =
     p.td = take(16 * (size_t)B);
     p.dz4 = take(4 * (size_t)B * HID);
     p.dz3 = take(4 * (size_t)bwd_split_rows(B) * FLAT);  // bwd_parts(B) partial planes
-    p.dz2 = take(4 * (size_t)bwd_split_rows(B) * P2 * C2);
+    p.dz2 = take(4 * (size_t)B * P2 * C2);
     p.dz1 = take(4 * (size_t)B * P1 * C1);
     p.part1 = B ? take(4 * (size_t)CONV1_WG_MAX_SPLITS * C1 * 256) : o;
     p.part2 = B ? take(4 * (size_t)WG_MAX_SPLITS * C2 * 16 * C1) : o;
@@ -614,8 +613,8 @@ int learner_steps(gorila_ctx* ctx, const gorila_params* params, int G, bool allo
         wv[g].theta = g < G ? theta[g] : theta_t;
         wv[g].w2t = at<float>(ctx, p.w2t + (size_t)g * W2T_BYTES);
         wv[g].w3t = at<float>(ctx, p.w3t + (size_t)g * W3T_BYTES);
-        wv[g].w3d = g < G ? at<float>(ctx, p.w3d + (size_t)g * W3T_BYTES) : nullptr;
-        wv[g].w2p = g < G ? at<float>(ctx, p.w2p + (size_t)g * W2T_BYTES) : nullptr;
+        wv[g].planes = bf16 ? 1 : FRAG_PLANES;
+        if (g < G) wv[g].fragd = at<uint16_t>(ctx, p.fragd + (size_t)g * FRAG_PLANES * FRAGD_BYTES);
     }
     // bf16 steps read W4 in place (the fc1 kernels widen it as they load), so
     // only the other tensors are widened
@@ -672,11 +671,11 @@ int learner_steps(gorila_ctx* ctx, const gorila_params* params, int G, bool allo
     float* coef = at<float>(ctx, p.coef);
     float* q = at<float>(ctx, p.q);
     float* bpart = at<float>(ctx, p.bpart);
-    GroupPtrs on{}, w3d{}, w2p{};
+    GroupPtrs on{};
+    GroupPtrs16 fragd{};
     for (int g = 0; g < G; ++g) {
         on.p[g] = theta[g];
-        w3d.p[g] = wv[g].w3d;
-        w2p.p[g] = wv[g].w2p;
+        fragd.p[g] = wv[g].fragd;
     }
     const int64_t part_stride = (int64_t)S * b * HID;  // fc1 partials of one forward group
     {
@@ -698,14 +697,15 @@ int learner_steps(gorila_ctx* ctx, const gorila_params* params, int G, bool allo
                                           at<float>(ctx, p.hpart), kp, sw, bf16, st);
     }
     {
-        StageTimer t(ctx, ST_CONV3_BWD);
-        s3 = launch_conv3_backward(dz3, w3d, G, h2, b, dz2, at<float>(ctx, p.part3),
-                                   bpart + 2 * BIAS_PART_STRIDE, kp, bf16, st);
+        StageTimer t(ctx, ST_CONV_DGRAD);
+        launch_bwd_data(dz3, kp, h2, h1, fragd, G, b, dz2, dz1, bf16, ctx->cus, st);
     }
     {
-        StageTimer t(ctx, ST_CONV2_BWD);
-        s2 = launch_conv2_backward(dz2, w2p, G, h1, b, dz1, at<float>(ctx, p.part2),
-                                   bpart + BIAS_PART_STRIDE, kp, bf16, st);
+        StageTimer t(ctx, ST_CONV_WGRAD);
+        launch_conv_wgrad(kp > 1 ? dz3 + (int64_t)kp * B * FLAT : dz3, bf16 && kp == 1, h2, dz2, h1, G, b,
+                          at<float>(ctx, p.part3), at<float>(ctx, p.part2),
+                          bpart + 2 * BIAS_PART_STRIDE, bpart + BIAS_PART_STRIDE, &s3, &s2, bf16,
+                          ctx->cus, st);
     }
     {
         StageTimer t(ctx, ST_CONV1_WGRAD);

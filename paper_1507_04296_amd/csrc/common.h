@@ -124,13 +124,8 @@ struct LdsTile {
     }
 };
 
-// Loaders keep per-quad state in arrays of MAXQ entries.  A loader may also
-// have prep(kc), called once per chunk before its load(kc, j) calls (an RMAJ
-// loader's quads share one k, so per-k work can be done there once).
+// Loaders keep per-quad state in arrays of MAXQ entries.
 constexpr int MAXQ = 4;
-template <class T, class = void> struct HasPrep : std::false_type {};
-template <class T>
-struct HasPrep<T, std::void_t<decltype(std::declval<T&>().prep(0))>> : std::true_type {};
 // An epilogue with `static constexpr bool MASK = true` only tests pre > 0.
 template <class T, class = void> struct IsMaskEpi : std::false_type {};
 template <class T>
@@ -347,8 +342,6 @@ __device__ __forceinline__ void mfma_gemm(float* smem, int kc_begin, int kc_end,
     // with (kc - kc_begin) % 2 == s.
     f32x4 ra0[LA::NQ], rb0[LB::NQ], ra1[LA::NQ], rb1[LB::NQ];
     auto gload = [&](int kc, f32x4* ra, f32x4* rb) {
-        if constexpr (HasPrep<LoadA>::value) la.prep(kc);
-        if constexpr (HasPrep<LoadB>::value) lb.prep(kc);
 #pragma unroll
         for (int j = 0; j < LA::NQ; ++j) ra[j] = la.load(kc, j);
 #pragma unroll
@@ -574,17 +567,6 @@ __device__ __forceinline__ void mfma_gemm(float* smem, int kc_begin, int kc_end,
                     epi(row, col, acc[i][j][r], pre[i][j][r]);
             }
 }
-
-// Epilogue writing scale * C into a row-major [rows][ld] buffer at column col0.
-struct PartialEpi {
-    float* out;
-    int ld, col0;
-    float scale;
-    __device__ float pre(int, int) const { return 0.0f; }
-    __device__ void operator()(int row, int col, float v, float) const {
-        out[(int64_t)row * ld + col0 + col] = v * scale;
-    }
-};
 
 // Butterfly sum over a wave64: every lane ends with the same bit pattern.
 __device__ inline float wave_sum(float v) {

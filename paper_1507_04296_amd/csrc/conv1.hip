@@ -3,6 +3,7 @@
 // exact integers; the 1/255 input scale is applied once in each epilogue.
 #include "common.h"
 #include "kernels.h"
+#include "planes.h"
 
 #include <type_traits>
 
@@ -199,9 +200,6 @@ constexpr int C1W_CH = C1W_XR * 4 * 2 * C1W_QS;  // stage elements per channel
 constexpr int C1W_PLANE = 4 * 16 * 64;  // floats: one wave's accumulators
 constexpr size_t C1W_SMEM = C1W_WAVES * sizeof(C1wStage) > 4 * C1W_WAVES * C1W_PLANE
                                 ? C1W_WAVES * sizeof(C1wStage) : 4 * C1W_WAVES * C1W_PLANE;
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // dz1 of a bf16 step (WP = 1) arrives rounded to bf16 ([n][20][20][32] bit
 // patterns); it is widened exactly as it is loaded.

@@ -43,16 +43,14 @@ void launch_insert(uint8_t* frames, uint8_t* ep_start, int32_t* action, float* r
 //  frag: the forward operands of trunk.hip, `planes` bf16 planes each (below)
 //  w2t [16][64][32]: W2[o][c][u][v] at [(u,v)][o][c]   (conv2 forward)
 //  w3t [9][64][64]:  W3[o][c][u][v] at [(u,v)][o][c]   (conv3 forward)
-//  w3d [9][64][64]:  W3[o][c][u][v] at [(u,v)][c][o]   (conv3 data gradient)
-//  w2p [4][4][32][64]: W2[o][c][u][v] at [(u/2,v/2)][(u%2,v%2)][c][o]  (conv2 data gradient)
+//  fragd: the data-gradient operands of bwd.hip, `planes` planes each
 struct WeightViews {
     const float* theta;   // flat parameters
     uint16_t* frag = nullptr;
     int planes = 0;       // 3 for fp32 weights, 1 for bf16 ones
     float* w2t = nullptr;
     float* w3t = nullptr;
-    float* w3d = nullptr;
-    float* w2p = nullptr;
+    uint16_t* fragd = nullptr;
     // when not null: the same parameters as bf16 bit patterns, which the
     // packing reads (and widens exactly) instead of theta, so that it need
     // not wait for theta's widened copy
@@ -71,8 +69,14 @@ struct WeightViewSet {
 //   conv1: f = FRAG1 + 2 * step + channel tile; 8 steps of 32 in OIHW order
 //   conv2: f = FRAG2 + 4 * tap + channel tile; 32 input channels
 //   conv3: f = FRAG3 + 4 * (2 * tap + input channel half) + channel tile
+// Data-gradient fragments, rows = input channels, reduction = 32 of the 64
+// output channels o (half):
+//   conv3: f = FRAGD3 + 4 * (2 * tap + half) + channel tile
+//   conv2: f = FRAGD2 + 16 * (2 py + px) + 2 * (2 * (2 du + dv) + half) + channel tile
+//          (tap u = 2 du + py, v = 2 dv + px)
 constexpr int FRAG1 = 0, FRAG2 = 16, FRAG3 = 80, NFRAG = 152;
-constexpr size_t FRAG_BYTES = (size_t)NFRAG * 1024;  // per plane
+constexpr int FRAGD3 = 0, FRAGD2 = 72, NFRAGD = 136;
+constexpr size_t FRAG_BYTES = (size_t)NFRAG * 1024, FRAGD_BYTES = (size_t)NFRAGD * 1024;  // per plane
 
 // Block `blk` of `nblk` (256 threads each) of one net's packing.  Every
 // destination is written in index order (coalesced); the scattered reads come
@@ -82,6 +86,21 @@ __device__ inline void prep_weights_part(const WeightViews& v, int blk, int nblk
     // W2 [o][c][u][v], 64 x 32 x 4 x 4; W3 [o][c][u][v], 64 x 64 x 3 x 3
     auto W = [&](int64_t i) {
         return v.theta16 ? __uint_as_float((uint32_t)v.theta16[i] << 16) : v.theta[i];
+    };
+    // lane l of fragment f: eight values from `at`, `step` apart
+    auto pack = [&](uint16_t* frag, int f, int l, int64_t at, int step) {
+        float w[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[e] = W(at + e * step);
+        for (int pl = 0; pl < v.planes; ++pl) {
+            bf16x8 b;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                b[e] = (__bf16)w[e];
+                w[e] -= (float)b[e];  // exact
+            }
+            *(bf16x8*)(frag + ((size_t)(f * v.planes + pl) * 64 + l) * 8) = b;
+        }
     };
     const int stride = nblk * 256;
     for (int d = blk * 256 + (int)threadIdx.x; v.frag && d < NFRAG * 64; d += stride) {
@@ -100,39 +119,28 @@ __device__ inline void prep_weights_part(const WeightViews& v, int blk, int nblk
             at = OFF_W3 + (o * 64 + (s & 1) * 32 + 8 * q) * 9 + (s >> 1);
             step = 9;
         }
-        float w[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) w[e] = W(at + e * step);
-        for (int pl = 0; pl < v.planes; ++pl) {
-            bf16x8 b;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                b[e] = (__bf16)w[e];
-                w[e] -= (float)b[e];  // exact
-            }
-            *(bf16x8*)(v.frag + ((size_t)(f * v.planes + pl) * 64 + l) * 8) = b;
+        pack(v.frag, f, l, at, step);
+    }
+    for (int d = blk * 256 + (int)threadIdx.x; v.fragd && d < NFRAGD * 64; d += stride) {
+        const int f = d >> 6, l = d & 63, q = l >> 4, c16 = l & 15;
+        if (f < FRAGD2) {
+            const int s = f >> 2, c = (f & 3) * 16 + c16, o = (s & 1) * 32 + 8 * q;
+            pack(v.fragd, f, l, OFF_W3 + (o * 64 + c) * 9 + (s >> 1), 576);
+        } else {
+            const int e = f - FRAGD2, ph = e >> 4, s = (e >> 1) & 7, c = (e & 1) * 16 + c16;
+            const int u = 2 * (s >> 2) + (ph >> 1), vv = 2 * ((s >> 1) & 1) + (ph & 1);
+            const int o = (s & 1) * 32 + 8 * q;
+            pack(v.fragd, f, l, OFF_W2 + (o * 32 + c) * 16 + u * 4 + vv, 512);
         }
     }
+    if (!v.w2t) return;
     for (int d = blk * 256 + (int)threadIdx.x; d < 16 * 64 * 32; d += stride) {
-        if (v.w2t) {  // w2t[t][o][c], t = u*4 + v
-            const int c = d & 31, o = (d >> 5) & 63, t = d >> 11;
-            v.w2t[d] = W(OFF_W2 + (o * 32 + c) * 16 + t);
-        }
-        if (v.w2p) {  // w2p[tp][phase][c][o]: tap pair (u/2, v/2), stride phase (u%2, v%2)
-            const int o = d & 63, c = (d >> 6) & 31, phase = (d >> 11) & 3, tp = d >> 13;
-            const int u = (tp >> 1) * 2 + (phase >> 1), vv = (tp & 1) * 2 + (phase & 1);
-            v.w2p[d] = W(OFF_W2 + ((o * 32 + c) * 4 + u) * 4 + vv);
-        }
+        const int c = d & 31, o = (d >> 5) & 63, t = d >> 11;  // w2t[t][o][c], t = u*4 + v
+        v.w2t[d] = W(OFF_W2 + (o * 32 + c) * 16 + t);
     }
     for (int d = blk * 256 + (int)threadIdx.x; d < 9 * 64 * 64; d += stride) {
-        if (v.w3t) {  // w3t[t][o][c], t = u*3 + v
-            const int c = d & 63, o = (d >> 6) & 63, t = d >> 12;
-            v.w3t[d] = W(OFF_W3 + (o * 64 + c) * 9 + t);
-        }
-        if (v.w3d) {  // w3d[t][c][o]
-            const int o = d & 63, c = (d >> 6) & 63, t = d >> 12;
-            v.w3d[d] = W(OFF_W3 + (o * 64 + c) * 9 + t);
-        }
+        const int c = d & 63, o = (d >> 6) & 63, t = d >> 12;  // w3t[t][o][c], t = u*3 + v
+        v.w3t[d] = W(OFF_W3 + (o * 64 + c) * 9 + t);
     }
 }
 
@@ -238,32 +246,30 @@ void launch_td_head(const float* fc1part_online, const float* fc1part_target, in
                     float* td, float* dz4, hipStream_t st);
 
 // Backward of `groups` learner groups of n rows each (group g: rows
-// g*n .. g*n+n-1 of every per-sample tensor, parameters of set g), three
-// launches of independent jobs each:
-//  fc1: dz3 = [h3 > 0] W4^T dz4 (stored [b][p][o]), dW4 and db4 into
-//       grads + g * grads_stride, and row-block partials of dW5, db5 and the
-//       loss (returns row blocks per group);
-//  conv3: dz2 and split partials of dW3 / db3 (returns splits per group);
-//  conv2: dz1 and split partials of dW2 / db2 (returns splits per group).
-// kp: dz3 / dz2 partial planes, each groups * n rows long; fc1 writes kp
-// planes of dz3, conv3 reads them and writes kp planes of dz2, conv2 reads
-// those.
+// g*n .. g*n+n-1 of every per-sample tensor, parameters of set g).
+// fc1: dz3 = [h3 > 0] W4^T dz4 (stored [b][p][o]) as kp partial planes, each
+// groups * n rows long, dW4 and db4 into grads + g * grads_stride, and
+// row-block partials of dW5, db5 and the loss (returns row blocks per group).
 int launch_fc1_backward(const float* dz4, const GroupPtrs& theta, const GroupPtrs16& w4b,
                         int groups, const float* h3,
                         const float* h4, const int32_t* a, const float* coef, const float* ell,
                         int n, int A, float* dz3, float* grads, int64_t grads_stride,
                         float* hpart, int kp, const SplitWs& sw, bool bf16, hipStream_t st);
-int launch_conv3_backward(const float* dz3, const GroupPtrs& w3d, int groups, const float* h2,
-                          int n, float* dz2, float* partial, float* bias_part, int kp, bool bf16,
-                          hipStream_t st);
-// dz1: fp32, or (bf16) the values rounded to bf16 in the same [n][20][20][32]
-// order, as the conv1 weight gradient below reads it.
-int launch_conv2_backward(const float* dz2, const GroupPtrs& w2p, int groups, const float* h1,
-                          int n, float* dz1, float* partial, float* bias_part, int kp, bool bf16,
-                          hipStream_t st);
+// dz2 [rows][81][64] and dz1 [rows][400][32] from kp planes of dz3 (bwd.hip),
+// whose fp32 sum is left as plane kp (kp > 1).
+// Outputs fp32, or (bf16) rounded to bf16, as the weight gradients read them;
+// frags.p[g]: learner group g's FRAGD fragments, three planes (bf16: one).
+void launch_bwd_data(float* dz3, int kp, const float* h2, const float* h1,
+                     const GroupPtrs16& frags, int groups, int n, float* dz2, float* dz1, bool bf16,
+                     int cus, hipStream_t st);
+// Split partials of dW3 / db3 and dW2 / db2 in one launch (wgrad.hip; dz3 and
+// dz2 as above, dz3 one plane); *s3, *s2: splits per group.
+void launch_conv_wgrad(const float* dz3, bool dz3_bf16, const float* h2, const float* dz2, const float* h1,
+                       int groups, int n, float* part3, float* part2, float* bias3, float* bias2,
+                       int* s3, int* s2, bool bf16, int cus, hipStream_t st);
 // ftab: [groups * n][4] frame pointers of the online states (null: zero-filled);
 // zero_frame: FRAME_BYTES of zeros, read in place of a null frame; dz1 as
-// launch_conv2_backward wrote it (bf16 bit patterns when bf16).
+// launch_bwd_data wrote it (bf16 bit patterns when bf16).
 void launch_conv1_wgrad(const float* dz1, const uint8_t* const* ftab, const uint8_t* zero_frame,
                         int groups, int n,
                         float* partial, float* bias_part, int max_splits, int* splits_out,
@@ -308,18 +314,15 @@ void launch_params_sync(const float* src, void* dst, int64_t n, int copies, bool
 constexpr int TARGET_WGS = 1024;             // split-K launches aim at ~4 workgroups per CU
 constexpr int FC1_MAX_SPLITS = 14;
 constexpr int WG_MAX_SPLITS = 256;
-constexpr int CONV3_WG_SPLITS = 114;         // 9 column tiles x 114 splits ~ 1024 workgroups
-constexpr int CONV2_WG_SPLITS = 64;          // 8 column tiles x 64 splits
 constexpr int CONV1_WG_MAX_SPLITS = 512;
-// Small batches split the fc1 and conv3 data gradients over the reduction:
-// with B learner rows, dz3 and dz2 arrive as bwd_parts(B) partial planes
-// (each already masked by the ReLU, which is linear in them) that the conv3
-// and conv2 backward loaders add in plane order.  bwd_split_rows(B) >=
-// bwd_parts(B) * B rows are reserved per tensor; it never decreases with B,
-// so a workspace sized for a batch serves every smaller one.
+// Small batches split the fc1 data gradient over the reduction: with B learner
+// rows, dz3 arrives as bwd_parts(B) partial planes (each already masked by the
+// ReLU, which is linear in them) that its readers add in plane order.
+// bwd_split_rows(B) rows hold them and their sum; it never decreases with B, so
+// a workspace sized for a batch serves every smaller one.
 __host__ __device__ constexpr int bwd_parts(int64_t rows) { return rows <= 64 ? 4 : rows <= 128 ? 2 : 1; }
 __host__ __device__ constexpr int64_t bwd_split_rows(int64_t rows) {
-    return rows <= 64 ? 4 * rows : rows <= 256 ? 256 : rows;
+    return rows <= 64 ? 5 * rows : rows <= 384 ? 384 : rows;
 }
 constexpr int BIAS_PART_STRIDE = 512 * 64;  // floats per layer in bias_part
 constexpr int HEAD_MAX_BLOCKS = 16;          // row blocks of the head partials, per group

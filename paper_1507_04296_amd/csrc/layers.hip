@@ -1,4 +1,5 @@
-// Convolution 2/3 and FC-512 layers, forward and backward, as implicit GEMMs
+// Convolution 2/3 and FC-512 layers, forward, weight gradients and (FC-512)
+// data gradient, as implicit GEMMs
 // on the fp32 MFMA tile engine (common.h).  Shapes follow Section 5.1 of the
 // paper; the backward pass is the exact gradient of those layers (eq. (2)
 // needs grad_theta Q(s, a; theta)).
@@ -14,47 +15,11 @@
 
 namespace gorila {
 
-// Output positions of an N x N data-gradient grid (kernel K taps per axis
-// over an IN x IN input, stride-1 form) in decreasing order of valid taps,
-// then raster order.  The data-gradient workgroups of a launch go longest
-// first, so the short border positions fill in at the end instead of long
-// interior ones trailing the launch.
-template <int N, int K, int IN>
-struct LongestFirst {
-    unsigned char pos[N * N];
-    static constexpr int taps(int y) {
-        return (y < K - 1 ? y : K - 1) - (y - (IN - 1) > 0 ? y - (IN - 1) : 0) + 1;
-    }
-    constexpr LongestFirst() : pos() {
-        int r = 0;
-        for (int want = K * K; want >= 1; --want)
-            for (int p = 0; p < N * N; ++p)
-                if (taps(p / N) * taps(p % N) == want) pos[r++] = (unsigned char)p;
-    }
-};
-
-// Gradients handed from one backward launch to the next (dz3, dz2): fp32, or
-// in bf16 steps whose reductions are not cut into parts (KP = 1) bf16,
-// rounded once by the producer to the precision the consumer's products take
-// them in (half the bytes written and read).
-template <int BF, int KP> using GradT = std::conditional_t<BF == 1 && KP == 1, uint16_t, float>;
-__device__ inline f32x4 ldq(const float* p) { return ld4(p); }
-__device__ inline f32x4 ldq(const uint16_t* p) {  // four bf16 values, widened exactly
-    const uint2 v = *(const uint2*)p;
-    return f32x4{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
-                 __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u)};
-}
+// dz3 leaves the fc1 backward as fp32, or in bf16 steps whose reduction is not
+// cut into parts (kp = 1) as bf16, rounded once to the precision its readers'
+// products take it in (half the bytes written and read).
 __device__ inline void stg(float* p, float v) { *p = v; }
 __device__ inline void stg(uint16_t* p, float v) { *p = __builtin_bit_cast(uint16_t, (__bf16)v); }
-
-// Quad at p summed over the KP partial planes p, p + ps, ... in plane order.
-template <int KP, class T>
-__device__ __forceinline__ f32x4 ld4_parts(const T* p, int64_t ps) {
-    f32x4 v = ldq(p);
-#pragma unroll
-    for (int s = 1; s < KP; ++s) v += ldq(p + s * ps);
-    return v;
-}
 
 // ---------------------------------------------------------------------------
 // conv2 forward: h2[m][o] = relu(b2[o] + sum_{u,v,c} W2[o][c][u][v] h1[b][2i+u][2j+v][c])
@@ -440,7 +405,7 @@ struct Fc1DgradJob {
         const int r0 = (t % mt) * 64, c0 = (t / mt) * 64;  // row tiles of one W4 column block adjacent
         const int64_t rows = (int64_t)g * n;
         RowMajorK la{dz4 + rows * HID, n, r0, HID};
-        const bool half = BF == 1 && kp == 1;  // dz3 as GradT<BF, kp>
+        const bool half = BF == 1 && kp == 1;  // dz3 as bf16
         Dz3NhwcStore epi{half ? nullptr : dz3 + part * (int64_t)groups * n * FLAT + rows * FLAT,
                          half ? (uint16_t*)dz3 + rows * FLAT : nullptr, h3 + rows * FLAT, n, r0, c0};
         // small-batch parts keep runtime bounds; whole tiles compile-time ones
@@ -601,388 +566,6 @@ int launch_fc1_backward(const float* dz4, const GroupPtrs& theta, const GroupPtr
     if (bf16) go(std::integral_constant<int, 1>{});
     else go(std::integral_constant<int, 0>{});
     return row_blocks;
-}
-
-// ---------------------------------------------------------------------------
-// conv3 data gradient (stride 1): dh2[b][y][x][c] = sum_{u,v,o} W3[o][c][u][v]
-// dz3[b][y-u][x-v][o] over in-range (y-u, x-v); then dz2 = dh2 * [h2 > 0].
-// A workgroup owns one output position (y, x) for 64 samples, so the taps that
-// fall outside the 7x7 input are the same for every row and are left out of
-// the reduction: only the 1..9 valid taps x 64 channels are multiplied.
-// rows b, cols c (64), reduction (valid tap, o) in chunks of 32 o.
-// ---------------------------------------------------------------------------
-template <int KP, class T>
-struct Conv3DgradA {  // KMAJ quads dz3[b][p][o..o+3] at p = (y-u)*7 + (x-v)
-    const T* dz3;
-    int n, b0, y, x, u0, v0, nv;
-    int64_t ps;  // KP planes of dz3, ps elements apart
-    const T* base[MAXQ];
-    __device__ void init(int j, int row, int k) {
-        const int b = b0 + row;
-        base[j] = dz3 + (int64_t)(b < n ? b : 0) * FLAT + k;  // rows past n: never stored
-    }
-    __device__ f32x4 load(int kc, int j) const {
-        const int t = kc >> 1, u = u0 + t / nv, v = v0 + t % nv;
-        return ld4_parts<KP>(base[j] + ((y - u) * H3 + (x - v)) * C3 + (kc & 1) * BK, ps);
-    }
-};
-struct Conv3DgradB {  // w3d[(u,v)][c][o], rows c, quads along o
-    const float* w3d;
-    int u0, v0, nv;
-    const float* base[MAXQ];
-    __device__ void init(int j, int row, int k) { base[j] = w3d + row * C3 + k; }
-    __device__ f32x4 load(int kc, int j) const {
-        const int t = kc >> 1, tap = (u0 + t / nv) * K3 + v0 + t % nv;
-        return ld4(base[j] + tap * C2 * C3 + (kc & 1) * BK);
-    }
-};
-template <class T>
-struct Conv3DgradStore {
-    static constexpr bool MASK = true;
-    T* dz2;
-    const float* h2;
-    int n, b0, pos;
-    __device__ float pre(int row, int col) const {
-        const int b = b0 + row;
-        return h2[((int64_t)(b < n ? b : 0) * P2 + pos) * C2 + col];
-    }
-    __device__ void operator()(int row, int col, float v, float m) const {
-        const int b = b0 + row;
-        if (b >= n) return;
-        stg(dz2 + ((int64_t)b * P2 + pos) * C2 + col, m > 0.0f ? v : 0.0f);
-    }
-};
-
-// dz3 arrives as KP partial planes, and KP > 1 also cuts the reduction over
-// (tap, o) into KP parts, each writing its own masked dz2 plane.
-template <int BF, int KP>
-struct Conv3DgradJob {
-    const float* dz3;
-    GroupPtrs w3d;
-    const float* h2;
-    float* dz2;
-    int n, groups;
-    static constexpr int PA = BF ? BF_GRAD : 0, PB = BF ? BF_WEIGHT : 0;
-    using SH = GemmShape<64, 64, KMAJ, KMAJ, PA, PB>;
-    static constexpr int SMEM = SH::SMEM_FLOATS;
-    __host__ __device__ int tiles() const { return P2 * ((n + 63) / 64); }
-    __host__ __device__ int blocks() const { return pad_xcd(tiles() * groups * KP); }
-    __device__ void run(int bid, float* smem) const {
-        int t = xcd_tile(bid, blocks());
-        if (t >= tiles() * groups * KP) return;
-        const int part = t / (tiles() * groups);
-        t -= part * tiles() * groups;
-        const int g = t / tiles();
-        t -= g * tiles();
-        const int64_t rows = (int64_t)g * n, plane = (int64_t)groups * n;
-        constexpr LongestFirst<H2, K3, H3> ORDER{};
-        // the position is uniform over the workgroup: keep it (and what derives
-        // from it) in scalar registers
-        const int pos = __builtin_amdgcn_readfirstlane(ORDER.pos[t % P2]);
-        const int y = pos / H2, x = pos - y * H2, b0 = (t / P2) * 64;
-        const int u0 = max(0, y - (H3 - 1)), u1 = min(K3 - 1, y);
-        const int v0 = max(0, x - (H3 - 1)), v1 = min(K3 - 1, x);
-        const int nv = v1 - v0 + 1, taps = (u1 - u0 + 1) * nv;
-        using G = GradT<BF, KP>;
-        Conv3DgradA<KP, G> la{(const G*)dz3 + rows * FLAT, n, b0, y, x, u0, v0, nv, plane * FLAT};
-        Conv3DgradB lb{w3d.p[g], u0, v0, nv};
-        Conv3DgradStore<G> epi{(G*)dz2 + (part * plane + rows) * P2 * C2, h2 + rows * P2 * C2, n, b0, pos};
-        mfma_gemm<64, 64, 2, KMAJ, KMAJ, PA, PB>(smem, part * 2 * taps / KP, (part + 1) * 2 * taps / KP,
-                                                 la, lb, epi);
-    }
-};
-
-// ---------------------------------------------------------------------------
-// conv3 weight gradient: dW3[o][c][u][v] = sum_{b,i,j} dz3[b][i][j][o] h2[b][i+u][j+v][c]
-// rows o (64), cols (tap, c): one tap of 64 channels per column tile,
-// reduction over the n*49 output pixels, split across workgroups.
-// partial[s][o][tap*64 + c].
-// ---------------------------------------------------------------------------
-template <int KP, class T>
-struct Conv3WgradA {  // RMAJ quads dz3[b][p][o0..o0+3] at one output pixel m = (b, p)
-    const T* dz3;
-    int npix;
-    int64_t ps;  // KP planes of dz3, ps elements apart
-    int o0[MAXQ], kk[MAXQ];
-    __device__ void init(int j, int row, int k) { o0[j] = row; kk[j] = k; }
-    __device__ f32x4 load(int kc, int j) const {
-        const int m = kc * BK + kk[j];
-        return sel4(m < npix, ld4_parts<KP>(dz3 + (int64_t)(m < npix ? m : 0) * C3 + o0[j], ps));
-    }
-};
-struct Conv3WgradB {  // RMAJ quads: 4 channels of h2 at one (pixel, tap)
-    const float* h2;
-    int npix, tap;
-    int c0[MAXQ], kk[MAXQ];
-    const float* pix = nullptr;  // h2 at this chunk's (pixel, tap), set by prep
-    __device__ void init(int j, int row, int k) { c0[j] = row; kk[j] = k; }
-    __device__ void prep(int kc) {  // the thread's quads share one pixel
-        const int m = kc * BK + kk[0];
-        const int mm = m < npix ? m : 0;  // past the end: pixel 0 (A is zero there)
-        const int b = mm / P3, p = mm - b * P3, i = p / H3, jj = p - i * H3;
-        const int u = tap / 3, v = tap - u * 3;
-        pix = h2 + (((int64_t)b * H2 + i + u) * H2 + jj + v) * C2;
-    }
-    __device__ f32x4 load(int, int j) const { return ld4(pix + c0[j]); }
-};
-
-template <int BF, int KP>
-struct Conv3WgradJob {
-    const float* dz3;
-    const float* h2;
-    float* partial;
-    float* bias_part;
-    int n, splits, cps, groups;
-    static constexpr int PA = BF ? BF_GRAD : 0, PB = BF ? BF_ACT_WGRAD : 0;
-    using SH = GemmShape<64, 64, RMAJ, RMAJ, PA, PB>;
-    static constexpr int SMEM = SH::SMEM_FLOATS;
-    __host__ __device__ int blocks() const { return pad_xcd(9 * splits * groups); }
-    __device__ void run(int bid, float* smem) const {
-        const int t = xcd_tile(bid, blocks());
-        if (t >= 9 * splits * groups) return;
-        // the nine taps of one split share dz3 rows; s runs over (group, split)
-        const int tap = t % 9, s = t / 9, g = s / splits;
-        const int npix = n * P3, nchunks = (npix + BK - 1) / BK;
-        const int64_t rows = (int64_t)g * n;
-        const int ks = s - g * splits;
-        using G = GradT<BF, KP>;
-        Conv3WgradA<KP, G> la{(const G*)dz3 + rows * FLAT, npix, (int64_t)groups * n * FLAT};
-        Conv3WgradB lb{h2 + rows * P2 * C2, npix, tap};
-        PartialEpi epi{partial + (int64_t)s * C3 * 9 * C2, 9 * C2, tap * C2, 1.0f};
-        float* rs = tap == 0 ? bias_part + (int64_t)s * 64 : nullptr;
-        mfma_gemm<64, 64, 2, RMAJ, RMAJ, PA, PB>(smem, ks * cps, min(nchunks, (ks + 1) * cps), la, lb, epi, rs);
-    }
-};
-
-// Splits per group shrink with the group count so one launch stays near the
-// same number of workgroups; groups * splits stays within WG_MAX_SPLITS.
-template <int BF, int KP>
-static void conv3_backward_jobs(const float* dz3, const GroupPtrs& w3d, int groups, const float* h2,
-                                int n, float* dz2, float* partial, float* bias_part, int splits,
-                                int cps, hipStream_t st) {
-    launch_jobs(st, Conv3DgradJob<BF, KP>{dz3, w3d, h2, dz2, n, groups},
-                Conv3WgradJob<BF, KP>{dz3, h2, partial, bias_part, n, splits, cps, groups});
-}
-
-// f(integral_constant<int, k>) for the plane count k in {1, 2, 4}
-template <class F>
-static void with_parts(int k, F&& f) {
-    if (k == 4) f(std::integral_constant<int, 4>{});
-    else if (k == 2) f(std::integral_constant<int, 2>{});
-    else f(std::integral_constant<int, 1>{});
-}
-
-int launch_conv3_backward(const float* dz3, const GroupPtrs& w3d, int groups, const float* h2,
-                          int n, float* dz2, float* partial, float* bias_part, int kp, bool bf16,
-                          hipStream_t st) {
-    if (n <= 0) return 0;
-    const int nchunks = (n * P3 + BK - 1) / BK;
-    int splits = min(min(WG_MAX_SPLITS / groups, nchunks), max(1, CONV3_WG_SPLITS / groups));
-    const int cps = (nchunks + splits - 1) / splits;
-    splits = (nchunks + cps - 1) / cps;
-    with_parts(kp, [&](auto k) {
-        if (bf16)
-            conv3_backward_jobs<1, k.value>(dz3, w3d, groups, h2, n, dz2, partial, bias_part, splits,
-                                            cps, st);
-        else
-            conv3_backward_jobs<0, k.value>(dz3, w3d, groups, h2, n, dz2, partial, bias_part, splits,
-                                            cps, st);
-    });
-    return splits;
-}
-
-// ---------------------------------------------------------------------------
-// conv2 data gradient (stride 2).  Output pixel (2y'+py, 2x'+px) receives
-// taps u = py + 2du, v = px + 2dv from dz2[y'-du][x'-dv], du, dv in {0, 1}, so
-// the four stride phases (py, px) of one (y', x') read the same four dz2
-// pixels with different weights and no inserted zeros are multiplied.  A
-// workgroup owns one (y', x') for 64 samples and two or all four phases as
-// its columns (phase, c); taps that fall outside the 9x9 input are the same
-// for every row and column and are skipped.  Reduction (valid tap, o) in
-// chunks of 32 o; dz1 = dh1 * [h1 > 0].
-// ---------------------------------------------------------------------------
-template <int KP, class T>
-struct Conv2DgradA {  // KMAJ quads dz2[b][i][j][o..o+3]
-    const T* dz2;
-    int n, b0, yy, xx, du0, dv0, ndv;
-    int64_t ps;  // KP planes of dz2, ps elements apart
-    const T* base[MAXQ];
-    __device__ void init(int j, int row, int k) {
-        const int b = b0 + row;
-        base[j] = dz2 + (int64_t)(b < n ? b : 0) * P2 * C2 + k;  // rows past n: never stored
-    }
-    __device__ f32x4 load(int kc, int j) const {
-        const int t = kc >> 1, du = du0 + t / ndv, dv = dv0 + t % ndv;
-        return ld4_parts<KP>(base[j] + ((yy - du) * H2 + (xx - dv)) * C2 + (kc & 1) * BK, ps);
-    }
-};
-struct Conv2DgradB {  // w2p[(du,dv)][phase][c][o], rows (phase, c), quads along o
-    const float* w2p;
-    int du0, dv0, ndv;
-    const float* base[MAXQ];
-    __device__ void init(int j, int row, int k) { base[j] = w2p + row * C2 + k; }
-    __device__ f32x4 load(int kc, int j) const {
-        const int t = kc >> 1, tp = (du0 + t / ndv) * 2 + dv0 + t % ndv;
-        return ld4(base[j] + tp * 4 * C1 * C2 + (kc & 1) * BK);
-    }
-};
-// bf16 steps store dz1 rounded to bf16 (the precision the conv1 weight
-// gradient multiplies it in), half the bytes of the fp32 steps' dz1.
-template <int BF>
-struct Conv2DgradStore {
-    static constexpr bool MASK = true;
-    using T = std::conditional_t<BF == 1, uint16_t, float>;
-    T* dz1;
-    const float* h1;
-    int n, b0, yy, xx, c0;  // c0: the tile's first column (phase, c)
-    __device__ int64_t at(int b, int col) const {
-        const int phase = (c0 + col) >> 5, c = col & 31;
-        const int y = 2 * yy + (phase >> 1), x = 2 * xx + (phase & 1);
-        return (((int64_t)b * H1 + y) * H1 + x) * C1 + c;
-    }
-    __device__ float pre(int row, int col) const {
-        const int b = b0 + row;
-        return h1[at(b < n ? b : 0, col)];
-    }
-    __device__ void operator()(int row, int col, float v, float m) const {
-        const int b = b0 + row;
-        if (b >= n) return;
-        const float r = m > 0.0f ? v : 0.0f;
-        if constexpr (BF == 1) dz1[at(b, col)] = __builtin_bit_cast(uint16_t, (__bf16)r);
-        else dz1[at(b, col)] = r;
-    }
-};
-
-template <int BF, int KP>
-struct Conv2DgradJob {
-    const float* dz2;
-    GroupPtrs w2p;
-    const float* h1;
-    float* dz1;
-    int n, groups;
-    static constexpr int PA = BF ? BF_GRAD : 0, PB = BF ? BF_WEIGHT : 0;
-    // fp32: two phases per tile (more, smaller workgroups measured faster:
-    // 69 -> 67 us at batch 512, 19 -> 14.5 us at batch 32); bf16: all four
-    static constexpr int BN = BF ? 128 : 64, NCT = 128 / BN;
-    using SH = GemmShape<64, BN, KMAJ, KMAJ, PA, PB>;
-    static constexpr int SMEM = SH::SMEM_FLOATS;
-    __host__ __device__ int tiles() const { return 100 * NCT * ((n + 63) / 64); }
-    __host__ __device__ int blocks() const { return pad_xcd(tiles() * groups); }
-    __device__ void run(int bid, float* smem) const {
-        int t = xcd_tile(bid, blocks());
-        if (t >= tiles() * groups) return;
-        const int g = t / tiles();
-        t -= g * tiles();
-        const int64_t rows = (int64_t)g * n;
-        // the column tiles of one position adjacent, positions longest first
-        constexpr LongestFirst<10, 2, H2> ORDER{};
-        const int ct = t % NCT, b0 = (t / (100 * NCT)) * 64;
-        const int pos = __builtin_amdgcn_readfirstlane(ORDER.pos[(t / NCT) % 100]);  // uniform
-        const int yy = pos / 10, xx = pos % 10;
-        const int du0 = max(0, yy - (H2 - 1)), du1 = min(1, yy);
-        const int dv0 = max(0, xx - (H2 - 1)), dv1 = min(1, xx);
-        const int ndv = dv1 - dv0 + 1, taps = (du1 - du0 + 1) * ndv;
-        using G = GradT<BF, KP>;
-        Conv2DgradA<KP, G> la{(const G*)dz2 + rows * P2 * C2, n, b0, yy, xx, du0, dv0, ndv,
-                              (int64_t)groups * n * P2 * C2};
-        Conv2DgradB lb{w2p.p[g] + ct * BN * C2, du0, dv0, ndv};
-        Conv2DgradStore<BF> epi{(typename Conv2DgradStore<BF>::T*)dz1 + rows * P1 * C1, h1 + rows * P1 * C1,
-                                n, b0, yy, xx, ct * BN};
-        mfma_gemm<64, BN, 2, KMAJ, KMAJ, PA, PB>(smem, 0, 2 * taps, la, lb, epi);
-    }
-};
-
-// ---------------------------------------------------------------------------
-// conv2 weight gradient: dW2[o][c][u][v] = sum_{b,i,j} dz2[b][i][j][o] h1[b][2i+u][2j+v][c]
-// rows o (64), cols (tap, c) with two taps per 64-column tile, reduction over
-// the n*81 output pixels split across workgroups.  partial[s][o][tap*32 + c].
-// ---------------------------------------------------------------------------
-template <int KP, class T>
-struct Conv2WgradA {  // dz2 quads along o at one pixel
-    const T* dz2;
-    int npix;
-    int64_t ps;  // KP planes of dz2, ps elements apart
-    int o0[MAXQ], kk[MAXQ];
-    __device__ void init(int j, int row, int k) { o0[j] = row; kk[j] = k; }
-    __device__ f32x4 load(int kc, int j) const {
-        const int m = kc * BK + kk[j];
-        return sel4(m < npix, ld4_parts<KP>(dz2 + (int64_t)(m < npix ? m : 0) * C2 + o0[j], ps));
-    }
-};
-struct Conv2WgradB {  // h1 quads along c at one (pixel, tap)
-    const float* h1;
-    int npix, tap0;
-    int off[MAXQ], kk[MAXQ];
-    __device__ void init(int j, int row, int k) {
-        const int t = tap0 + (row >> 5), c0 = row & 31;
-        off[j] = ((t >> 2) * H1 + (t & 3)) * C1 + c0;
-        kk[j] = k;
-    }
-    const float* pix = nullptr;  // h1 at this chunk's pixel, set by prep
-    __device__ void prep(int kc) {  // the thread's quads share one pixel
-        const int m = kc * BK + kk[0];
-        const int mm = m < npix ? m : 0;  // past the end: pixel 0 (A is zero there)
-        const int b = mm / P2, p = mm - b * P2, i = p / H2, jj = p - i * H2;
-        pix = h1 + (((int64_t)b * H1 + S2 * i) * H1 + S2 * jj) * C1;
-    }
-    __device__ f32x4 load(int, int j) const { return ld4(pix + off[j]); }
-};
-
-template <int BF, int KP>
-struct Conv2WgradJob {
-    const float* dz2;
-    const float* h1;
-    float* partial;
-    float* bias_part;
-    int n, splits, cps, groups;
-    static constexpr int PA = BF ? BF_GRAD : 0, PB = BF ? BF_ACT_WGRAD : 0;
-    using SH = GemmShape<64, 64, RMAJ, RMAJ, PA, PB>;
-    static constexpr int SMEM = SH::SMEM_FLOATS;
-    __host__ __device__ int blocks() const { return pad_xcd(8 * splits * groups); }
-    __device__ void run(int bid, float* smem) const {
-        const int t = xcd_tile(bid, blocks());
-        if (t >= 8 * splits * groups) return;
-        // the column tiles of one split share dz2 rows; s runs over (group, split)
-        const int tap0 = (t % 8) * 2, s = t / 8, g = s / splits;
-        const int npix = n * P2, nchunks = (npix + BK - 1) / BK;
-        const int64_t rows = (int64_t)g * n;
-        const int ks = s - g * splits;
-        using G = GradT<BF, KP>;
-        Conv2WgradA<KP, G> la{(const G*)dz2 + rows * P2 * C2, npix, (int64_t)groups * n * P2 * C2};
-        Conv2WgradB lb{h1 + rows * P1 * C1, npix, tap0};
-        PartialEpi epi{partial + (int64_t)s * C2 * 16 * C1, 16 * C1, tap0 * C1, 1.0f};
-        float* rs = tap0 == 0 ? bias_part + (int64_t)s * 64 : nullptr;
-        mfma_gemm<64, 64, 2, RMAJ, RMAJ, PA, PB>(smem, ks * cps, min(nchunks, (ks + 1) * cps), la, lb, epi, rs);
-    }
-};
-
-// the weight-gradient workgroups are the longer ones (21 chunks against at
-// most 8 at batch 512): dispatched first, they do not trail the launch
-template <int BF, int KP>
-static void conv2_backward_jobs(const float* dz2, const GroupPtrs& w2p, int groups, const float* h1,
-                                int n, float* dz1, float* partial, float* bias_part, int splits,
-                                int cps, hipStream_t st) {
-    launch_jobs(st, Conv2WgradJob<BF, KP>{dz2, h1, partial, bias_part, n, splits, cps, groups},
-                Conv2DgradJob<BF, KP>{dz2, w2p, h1, dz1, n, groups});
-}
-
-int launch_conv2_backward(const float* dz2, const GroupPtrs& w2p, int groups, const float* h1,
-                          int n, float* dz1, float* partial, float* bias_part, int kp, bool bf16,
-                          hipStream_t st) {
-    if (n <= 0) return 0;
-    const int nchunks = (n * P2 + BK - 1) / BK;
-    int splits = min(min(WG_MAX_SPLITS / groups, nchunks), max(1, CONV2_WG_SPLITS / groups));
-    const int cps = (nchunks + splits - 1) / splits;
-    splits = (nchunks + cps - 1) / cps;
-    with_parts(kp, [&](auto k) {
-        if (bf16)
-            conv2_backward_jobs<1, k.value>(dz2, w2p, groups, h1, n, dz1, partial, bias_part, splits,
-                                            cps, st);
-        else
-            conv2_backward_jobs<0, k.value>(dz2, w2p, groups, h1, n, dz1, partial, bias_part, splits,
-                                            cps, st);
-    });
-    return splits;
 }
 
 // ---------------------------------------------------------------------------

@@ -1,0 +1,119 @@
+// fp32 products on v_mfma_f32_16x16x32_bf16: an operand is a sum of bf16
+// planes (three hold an fp32 value: hi + mid + lo, each the rounded remainder
+// of the previous, 8 + 8 + 8 significant bits; bf16 values are one plane), and
+// of the nine plane products of two fp32 operands the three below 2^-24 of the
+// value (mid*lo, lo*mid, lo*lo) are left out.  Each plane product is exact in
+// fp32, so only the accumulation rounds.
+//
+// Operand layout: lane l holds row (A) or column (B) l % 16 and the reduction
+// indices 8 (l / 16) .. +7; accumulator element e of lane l is row 4 (l / 16)
+// + e, column l % 16.
+#pragma once
+#include "common.h"
+
+namespace gorila {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// Four values as NP bf16 planes (two values per rounding; the remainders are exact).
+template <int NP>
+__device__ __forceinline__ void split4(f32x4 v, bf16x4 (&o)[NP]) {
+    f32x2 a{v[0], v[1]}, b{v[2], v[3]};
+#pragma unroll
+    for (int pl = 0; pl < NP; ++pl) {
+        const bf16x2 ha = __builtin_convertvector(a, bf16x2), hb = __builtin_convertvector(b, bf16x2);
+        o[pl] = __builtin_shufflevector(ha, hb, 0, 1, 2, 3);
+        if (pl + 1 < NP) {
+            const uint32_t ba = __builtin_bit_cast(uint32_t, ha), bb = __builtin_bit_cast(uint32_t, hb);
+            a = f32x2{a[0] - __uint_as_float(ba << 16), a[1] - __uint_as_float(ba & 0xffff0000u)};
+            b = f32x2{b[0] - __uint_as_float(bb << 16), b[1] - __uint_as_float(bb & 0xffff0000u)};
+        }
+    }
+}
+
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// A copy of a value that the compiler cannot see through: what derives from
+// it is computed where it is used, per sample, instead of being kept in
+// registers over the whole row loop.
+__device__ __forceinline__ int opaque(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// One reduction step of 32 for NC row tiles (operand a) and NT column tiles
+// (operand b): the leading products into hi, the others into lo.
+template <int PA, int PB, int NC, int NT>
+__device__ __forceinline__ void step_products(const bf16x8 (&a)[NC][PA], const bf16x8 (&b)[NT][PB],
+                                              f32x4 (&hi)[NC][NT], f32x4 (&lo)[NC][NT]) {
+#pragma unroll
+    for (int order = 0; order <= 2; ++order)
+#pragma unroll
+        for (int pa = 0; pa < PA; ++pa) {
+            const int pb = order - pa;
+            if (pb < 0 || pb >= PB) continue;
+#pragma unroll
+            for (int i = 0; i < NC; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    if (order == 0) hi[i][j] = mfma16(a[i][pa], b[j][pb], hi[i][j]);
+                    else lo[i][j] = mfma16(a[i][pa], b[j][pb], lo[i][j]);
+                }
+        }
+}
+
+// Quads of fp32 values or of bf16 bit patterns (widened exactly; stored rounded).
+__device__ inline f32x4 ldq(const float* p) { return ld4(p); }
+__device__ inline f32x4 ldq(const uint16_t* p) {
+    const uint2 v = *(const uint2*)p;
+    return f32x4{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
+                 __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u)};
+}
+__device__ inline void stq(float* p, f32x4 v) { *(f32x4*)p = v; }
+__device__ inline void stq(uint16_t* p, f32x4 v) {
+    bf16x4 o[1];
+    split4<1>(v, o);
+    *(bf16x4*)p = o[0];
+}
+
+template <int I, int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}
+
+// Products of R row tiles with the column tiles J0 .. J0 + C - 1: the leading
+// ones into hi, the others into lo.  Each plane pair is a round of R C
+// independent instructions; the scheduling barriers keep the rounds apart (the
+// compiler would run one accumulator's chain back to back, each waiting for
+// the one before) and let everything but matrix instructions pass.
+template <int J0, int P, int R, int C, int N>
+__device__ __forceinline__ void plane_products(const bf16x8 (&a)[R][P], const bf16x8 (&x)[C][P],
+                                               f32x4 (&hi)[R][N], f32x4 (&lo)[R][N]) {
+    auto round = [&](auto pc, auto qc, f32x4 (&acc)[R][N]) {
+        constexpr int pa = decltype(pc)::value, px = decltype(qc)::value;
+        if constexpr (pa < P && px < P) {
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+#pragma unroll
+                for (int j = 0; j < C; ++j) acc[i][J0 + j] = mfma16(a[i][pa], x[j][px], acc[i][J0 + j]);
+            __builtin_amdgcn_sched_barrier(0x7f6);
+        }
+    };
+    constexpr std::integral_constant<int, 0> I0{};
+    constexpr std::integral_constant<int, 1> I1{};
+    constexpr std::integral_constant<int, 2> I2{};
+    round(I0, I0, hi);
+    round(I0, I1, lo);
+    round(I1, I0, lo);
+    round(I0, I2, lo);
+    round(I1, I1, lo);
+    round(I2, I0, lo);
+}
+
+}  // namespace gorila

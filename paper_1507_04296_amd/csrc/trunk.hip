@@ -25,6 +25,7 @@
 // KB a sample with three planes.
 #include "common.h"
 #include "kernels.h"
+#include "planes.h"
 
 namespace gorila {
 
@@ -34,19 +35,21 @@ constexpr int TR_XPT = (TR_XV + TR_THREADS - 1) / TR_THREADS;
 constexpr int TR_T2 = 3;  // conv2: pixel tiles of 16 per wave (6 in all, 81 pixels)
 constexpr int TR_T3 = 2;  // conv3: 4 in all, 49 pixels
 
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
 // h1 in LDS: 64 bytes a pixel and plane, two pixels to a 128-byte line whose
-// eight 16-byte chunks are XOR-permuted by the line's number, so the stride-2
-// pixels that 16 lanes read at one chunk fall into different banks.
-__device__ inline int h1_off(int p, int chunk) {
-    const int line = p >> 1;
-    return line * 128 + (((((p & 1) << 2) | chunk) ^ (line & 7)) << 4);
+// eight 16-byte chunks are XOR-permuted by a key that runs on over the ends of
+// conv2's rows (9 y / 2 + x / 2), so the stride-2 pixels that 8 lanes read at
+// one chunk always fall into different banks.
+__device__ inline int h1_at(int line, int odd, int key, int chunk) {
+    return line * 128 + ((((odd << 2) | chunk) ^ (key & 7)) << 4);
+}
+__device__ inline int h1_off(int y, int x, int chunk) {
+    return h1_at(y * (H1 / 2) + (x >> 1), x & 1, (y >> 1) * H2 + (x >> 1), chunk);
 }
 constexpr int H1_PLANE = P1 * 64;
-// h2: 128 bytes a pixel and plane, chunks permuted by the pixel's number.
-__device__ inline int h2_off(int p, int chunk) { return p * 128 + ((chunk ^ (p & 7)) << 4); }
+// h2: 128 bytes a pixel and plane, chunks permuted by a key that runs on over
+// the ends of conv3's rows.
+__device__ inline int h2_at(int p, int key, int chunk) { return p * 128 + ((chunk ^ (key & 7)) << 4); }
+__device__ inline int h2_off(int y, int x, int chunk) { return h2_at(y * H2 + x, y * H3 + x, chunk); }
 constexpr int H2_PLANE = P2 * 128;
 
 template <int AP>
@@ -57,55 +60,6 @@ struct TrunkLds {
     static constexpr int X = STATE_BYTES * 2, H2 = AP * H2_PLANE, XCHG2 = TR_WAVES * TR_T2 * 1024;
     static constexpr int LO = cmax(H1, XCHG3), HI = cmax(X, H2 + XCHG2);
 };
-
-// Four values as AP bf16 planes (two values per rounding; the remainders are exact).
-template <int AP>
-__device__ __forceinline__ void split4(f32x4 v, bf16x4 (&o)[AP]) {
-    f32x2 a{v[0], v[1]}, b{v[2], v[3]};
-#pragma unroll
-    for (int pl = 0; pl < AP; ++pl) {
-        const bf16x2 ha = __builtin_convertvector(a, bf16x2), hb = __builtin_convertvector(b, bf16x2);
-        o[pl] = __builtin_shufflevector(ha, hb, 0, 1, 2, 3);
-        if (pl + 1 < AP) {
-            const uint32_t ba = __builtin_bit_cast(uint32_t, ha), bb = __builtin_bit_cast(uint32_t, hb);
-            a = f32x2{a[0] - __uint_as_float(ba << 16), a[1] - __uint_as_float(ba & 0xffff0000u)};
-            b = f32x2{b[0] - __uint_as_float(bb << 16), b[1] - __uint_as_float(bb & 0xffff0000u)};
-        }
-    }
-}
-
-__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-// A copy of a value that the compiler cannot see through: what derives from
-// it is computed where it is used, per sample, instead of being kept in
-// registers over the whole row loop.
-__device__ __forceinline__ int opaque(int v) {
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
-// One reduction step of 32 for NC channel tiles (weights w) and NT pixel tiles
-// (activations x): the leading products into hi, the others into lo.
-template <int WP, int AP, int NC, int NT>
-__device__ __forceinline__ void step_products(const bf16x8 (&w)[NC][WP], const bf16x8 (&x)[NT][AP],
-                                              f32x4 (&hi)[NC][NT], f32x4 (&lo)[NC][NT]) {
-#pragma unroll
-    for (int order = 0; order <= 2; ++order)
-#pragma unroll
-        for (int pw = 0; pw < WP; ++pw) {
-            const int px = order - pw;
-            if (px < 0 || px >= AP) continue;
-#pragma unroll
-            for (int i = 0; i < NC; ++i)
-#pragma unroll
-                for (int j = 0; j < NT; ++j) {
-                    if (order == 0) hi[i][j] = mfma16(w[i][pw], x[j][px], hi[i][j]);
-                    else lo[i][j] = mfma16(w[i][pw], x[j][px], lo[i][j]);
-                }
-        }
-}
 
 // WP planes of weights, AP of activations.  Samples r = blockIdx.x, +
 // gridDim.x, ...
@@ -154,7 +108,9 @@ __global__ __launch_bounds__(TR_THREADS) void trunk_fwd_kernel(
     const int c1t = wave & 1, pg = wave >> 1;
     // conv2, conv3: wave = (reduction half kh, pixel half mh, channel half nh)
     const int kh = wave & 1, mh = (wave >> 1) & 1, nh = wave >> 2;
-    int x1[7], p2[TR_T2], p3[TR_T3];  // LDS element of the frames / first pixel, per pixel tile
+    // per pixel tile: LDS element of the frames; line of h1 and pixel of h2 at
+    // tap (0, 0), and their keys (which are the output pixel's number)
+    int x1[7], p2[TR_T2], k2[TR_T2], p3[TR_T3], k3[TR_T3];
 #pragma unroll
     for (int k = 0; k < 7; ++k) {
         const int m = (pg + 4 * k < 25 ? pg + 4 * k : 0) * 16 + col, i = m / H1, j = m - i * H1;
@@ -163,12 +119,14 @@ __global__ __launch_bounds__(TR_THREADS) void trunk_fwd_kernel(
 #pragma unroll
     for (int k = 0; k < TR_T2; ++k) {
         const int m = min((mh * TR_T2 + k) * 16 + col, P2 - 1), i = m / H2, j = m - i * H2;
-        p2[k] = S2 * i * H1 + S2 * j;
+        p2[k] = i * H1 + j;
+        k2[k] = m;
     }
 #pragma unroll
     for (int k = 0; k < TR_T3; ++k) {
         const int m = min((mh * TR_T3 + k) * 16 + col, P3 - 1), i = m / H3, j = m - i * H3;
         p3[k] = i * H2 + j;
+        k3[k] = m;
     }
 
     // Weight fragments of a layer's step s into w[s & 1].  Two steps are in
@@ -262,7 +220,7 @@ __global__ __launch_bounds__(TR_THREADS) void trunk_fwd_kernel(
                     }
                     bf16x4 o[AP];
                     split4<AP>(v, o);
-                    const int off = h1_off(p, c0 >> 3) + ((c0 & 4) << 1);
+                    const int off = h1_off(p / H1, p % H1, c0 >> 3) + ((c0 & 4) << 1);
 #pragma unroll
                     for (int pl = 0; pl < AP; ++pl) *(bf16x4*)(s1 + pl * H1_PLANE + off) = o[pl];
                 }
@@ -279,14 +237,18 @@ __global__ __launch_bounds__(TR_THREADS) void trunk_fwd_kernel(
             for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int j = 0; j < TR_T2; ++j) hi[i][j] = lo[i][j] = f32x4{};
-            int px[TR_T2];
+            int px[TR_T2], kx[TR_T2];
 #pragma unroll
-            for (int j = 0; j < TR_T2; ++j) px[j] = opaque(p2[j]);
+            for (int j = 0; j < TR_T2; ++j) {
+                px[j] = opaque(p2[j]);
+                kx[j] = opaque(k2[j]);
+            }
             bf16x8 x[2][TR_T2][AP];
             auto xload = [&](int s) {
 #pragma unroll
                 for (int j = 0; j < TR_T2; ++j) {
-                    const int off = h1_off(px[j] + (2 * kh + (s >> 2)) * H1 + (s & 3), q);
+                    const int u = 2 * kh + (s >> 2), v = s & 3;
+                    const int off = h1_at(px[j] + u * (H1 / 2) + (v >> 1), v & 1, kx[j] + (u >> 1) * H2 + (v >> 1), q);
 #pragma unroll
                     for (int pl = 0; pl < AP; ++pl)
                         x[s & 1][j][pl] = *(const bf16x8*)(s1 + pl * H1_PLANE + off);
@@ -298,7 +260,7 @@ __global__ __launch_bounds__(TR_THREADS) void trunk_fwd_kernel(
 #pragma unroll
             for (int s = 0; s < 8; ++s) {
                 if (s + 1 < 8) xload(s + 1);
-                step_products<WP, AP, 2, TR_T2>(w[s & 1], x[s & 1], hi, lo);
+                step_products(w[s & 1], x[s & 1], hi, lo);
                 if (s + 2 < 8) wload(wf2, 4, 2, s + 2);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -325,7 +287,7 @@ __global__ __launch_bounds__(TR_THREADS) void trunk_fwd_kernel(
                 if (p < P2) {
                     bf16x4 o[AP];
                     split4<AP>(v, o);
-                    const int off = h2_off(p, c0 >> 3) + ((c0 & 4) << 1);
+                    const int off = h2_off(p / H2, p % H2, c0 >> 3) + ((c0 & 4) << 1);
 #pragma unroll
                     for (int pl = 0; pl < AP; ++pl) *(bf16x4*)(s2 + pl * H2_PLANE + off) = o[pl];
                 }
@@ -340,9 +302,12 @@ __global__ __launch_bounds__(TR_THREADS) void trunk_fwd_kernel(
             for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int j = 0; j < TR_T3; ++j) hi[i][j] = lo[i][j] = f32x4{};
-            int px[TR_T3];
+            int px[TR_T3], kx[TR_T3];
 #pragma unroll
-            for (int j = 0; j < TR_T3; ++j) px[j] = opaque(p3[j]);
+            for (int j = 0; j < TR_T3; ++j) {
+                px[j] = opaque(p3[j]);
+                kx[j] = opaque(k3[j]);
+            }
             const int el = opaque(lane), c0 = (nh * 2 + kh) * 16 + 4 * (el >> 4);
             const f32x4 bias = ld4(th + zero + OFF_B3 + c0);
             float* const out = h3 + (int64_t)r * FLAT;
@@ -351,7 +316,7 @@ __global__ __launch_bounds__(TR_THREADS) void trunk_fwd_kernel(
                 const int st = kh * 9 + s, tap = st >> 1, u = tap / 3, v = tap - 3 * u;
 #pragma unroll
                 for (int j = 0; j < TR_T3; ++j) {
-                    const int off = h2_off(px[j] + u * H2 + v, (st & 1) * 4 + q);
+                    const int off = h2_at(px[j] + u * H2 + v, kx[j] + u * H3 + v, (st & 1) * 4 + q);
 #pragma unroll
                     for (int pl = 0; pl < AP; ++pl)
                         x[s & 1][j][pl] = *(const bf16x8*)(s2 + pl * H2_PLANE + off);
@@ -361,12 +326,19 @@ __global__ __launch_bounds__(TR_THREADS) void trunk_fwd_kernel(
 #pragma unroll
             for (int s = 0; s < 9; ++s) {
                 if (s + 1 < 9) xload(s + 1);
-                step_products<WP, AP, 2, TR_T3>(w[s & 1], x[s & 1], hi, lo);
+                step_products(w[s & 1], x[s & 1], hi, lo);
                 if (s + 2 < 9) wload(wf3, 4, 2, s + 2);
                 // the next sample's frames come from memory: requested behind
                 // this sample's last weights, they are waited for by no one
                 // before they are staged
-                if (s == 6 && next < rows) fetch();
+                if (s == 6) {
+                    if (next < rows) {
+                        fetch();
+                    } else {  // nothing of this sample's frames stays in registers
+#pragma unroll
+                        for (int k = 0; k < TR_XPT; ++k) xv[k] = make_uint4(0, 0, 0, 0);
+                    }
+                }
                 __builtin_amdgcn_sched_barrier(0);
             }
             wload(wf1, 2, 1, 0);

@@ -1,0 +1,72 @@
+"""The convolutions' backward launches at the edges of their row counts: dz3 in
+four, two or one partial plane (up to 64, 128 and more learner rows), one or
+two samples a workgroup (256, and 512 with bf16 operands, run at once), sample
+ranges of unequal length, against the fp64 oracle; and twice for the same bits.
+Bars as everywhere (tests/parity.py): 1e-3 relative L2 a tensor, 2e-2 for bf16
+operands."""
+import numpy as np
+import pytest
+
+import parity
+from paper_1507_04296_amd import datagen
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _t(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _check(g, oracle_mod, call, thetas64, target64, inp, idx, b, A, tol):
+    grads, loss = call()
+    g2, l2 = call()
+    assert torch.equal(grads, g2) and torch.equal(loss, l2)
+    got, got_l = grads.cpu().numpy().reshape(len(thetas64), -1), loss.cpu().numpy()
+    net = oracle_mod.Net(n_actions=A)
+    for i, th in enumerate(thetas64):
+        rows = idx[i * b:(i + 1) * b]
+        ref = oracle_mod.learner_step(net, th, target64, inp.s[rows], inp.s2[rows], inp.a[rows],
+                                      inp.r[rows], inp.term[rows], inp.gamma, 1.0)
+        parity.assert_grads_close(got[i], ref["grads"], A, tol)
+        assert abs(got_l[i] - ref["loss"]) <= parity.LOSS_TOL * abs(ref["loss"])
+
+
+@pytest.fixture(scope="module")
+def oracle_mod():
+    import oracle
+    return oracle
+
+
+@pytest.mark.parametrize("B", [1, 2, 64, 65, 128, 129, 257, 513])
+def test_fp32_rows(oracle_mod, B):
+    import paper_1507_04296_amd as g
+    print(f"[gpu-case] conv backward fp32 B={B}", flush=True)
+    A = 5
+    inp = datagen.learner_inputs(7300 + B, B, A)
+    ctx = g.Context(B, A)
+    rep = g.Replay.stacked(_t(inp.s), _t(inp.s2), _t(inp.a), _t(inp.r), _t(inp.term))
+    th, tg, idx = _t(inp.theta), _t(inp.theta_target), _t(inp.idx)
+    _check(g, oracle_mod, lambda: g.learner_step(ctx, th, tg, A, rep, idx, inp.gamma, 1.0),
+           [inp.theta.astype(np.float64)], inp.theta_target.astype(np.float64), inp, inp.idx, B, A,
+           parity.GRAD_TOL)
+    ctx.check()
+    ctx.close()
+
+
+@pytest.mark.parametrize("G,b", [(2, 32), (2, 64), (3, 43), (16, 33)])
+def test_bf16_rows(oracle_mod, G, b):
+    import paper_1507_04296_amd as g
+    print(f"[gpu-case] conv backward bf16 G={G} b={b}", flush=True)
+    A = 5
+    inp = datagen.grouped_inputs(7400 + G * b, G, b, A)
+    ctx = g.Context(b, A, groups=G, dtype=g.GORILA_BF16)
+    rep = g.Replay.stacked(_t(inp.s), _t(inp.s2), _t(inp.a), _t(inp.r), _t(inp.term))
+    th, tg = _t(inp.theta_bf16.view(np.int16)), _t(inp.target_bf16.view(np.int16))
+    idx = np.arange(G * b, dtype=np.int64)
+    _check(g, oracle_mod,
+           lambda: g.learner_step_grouped(ctx, th, tg, A, rep, _t(idx), inp.gamma, 1.0),
+           [datagen.bf16_bits_to_f64(t) for t in inp.theta_bf16],
+           datagen.bf16_bits_to_f64(inp.target_bf16), inp, idx, b, A, parity.GRAD_TOL_BF16)
+    ctx.check()
+    ctx.close()
