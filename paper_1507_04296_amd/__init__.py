@@ -161,12 +161,18 @@ class Context:
                                            self.ws_bytes), "gorila_ctx_create")
         self.handle = h
 
-    def _stream(self):
+    def _stream(self) -> int:
+        """The handle of torch's current stream on the context's device.  Read
+        from the native accessor: building a torch.cuda.Stream object for it
+        took 3.2 of a call's 9.2 us of host time (replay insert), this 0.1."""
         import torch
-        return ctypes.c_void_p(torch.cuda.current_stream(self.device).cuda_stream)
+        index = self.device.index
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
 
     def bind_stream(self):
-        _check(lib().gorila_ctx_set_stream(self.handle, self._stream()), "gorila_ctx_set_stream")
+        rc = lib().gorila_ctx_set_stream(self.handle, self._stream())
+        if rc != 0:
+            _check(rc, "gorila_ctx_set_stream")
         return self.handle
 
     def check(self) -> None:
