@@ -1,0 +1,61 @@
+"""Edges of the parameter-server kernels: vector remainders and unaligned rows of
+the pull and the apply, and AdaGrad's square root and division outside the
+range of their fast forms."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("period", [0, 10])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("n,copies", [(1, 1), (3, 2), (4, 3), (5, 16), (1023, 5), (4097, 64)])
+def test_sync_remainders(n, copies, bf16, period):
+    import paper_1507_04296_amd as g
+    dt = torch.bfloat16 if bf16 else torch.float32
+    src = torch.randn(n, device="cuda")
+    # one element before and after: rows start at any element's address, and
+    # nothing around them may change
+    buf = torch.full((copies * n + 2,), 7.0, dtype=dt, device="cuda")
+    dst = buf[1:-1].view(copies, n)
+    held = torch.arange(copies, dtype=torch.int64, device="cuda")  # 0, 1, ...
+    now = torch.tensor([25], dtype=torch.int64, device="cuda")
+    synced = torch.full((copies,), 9, dtype=torch.uint8, device="cuda")
+    ctx = g.Context(0, 4)
+    g.gorila_params_sync(ctx, src, dst, held, now, period, synced)
+    ctx.check()
+    due = np.ones(copies, bool) if period == 0 else 25 // period > np.arange(copies) // period
+    assert synced.cpu().numpy().tolist() == due.astype(int).tolist()
+    assert held.cpu().numpy().tolist() == np.where(due, 25, np.arange(copies)).tolist()
+    for c in range(copies):
+        assert torch.equal(dst[c], src.to(dt) if due[c] else torch.full_like(dst[c], 7.0))
+    assert float(buf[0]) == 7.0 and float(buf[-1]) == 7.0
+
+
+@pytest.mark.parametrize("lr,eps", [(0.01, 1e-6), (1.0, 1e30), (1e-3, float("inf")), (1e20, 1e-3)])
+def test_adagrad_extremes(lr, eps):
+    """Each operation of the update rounds once: against 64 bits the step's error
+    is a few units of its last place (4 * 2^-23 of the step, plus theta's own), as
+    long as lr * g is finite (here at most 1e20 * 1e14 < 3.4e38)."""
+    import paper_1507_04296_amd as g
+    h = np.array([0, 0, 1e-38, 1e-30, 1e-24, 2.0**-80, 1e-3, 1.0, 3e7, 2.0**80, 1e30, 3e38], np.float32)
+    gr = np.array([0, 1e-20, 0, 1e-16, 1e-13, 1e-13, -1e-2, 0.3, -5e3, 1e11, 1e14, 1e5], np.float32)
+    th = np.linspace(-1, 1, h.size).astype(np.float32)
+    t = lambda a: torch.from_numpy(a.copy()).cuda()
+    T, H, G = t(th), t(h), t(gr[None])
+    one = lambda v: torch.tensor([v], dtype=torch.int64, device="cuda")
+    applied = torch.empty(1, dtype=torch.uint8, device="cuda")
+    ctx = g.Context(0, 4)
+    g.gorila_ps_apply(ctx, T, H, G, one(0), one(0), 0, lr, eps, applied)
+    ctx.check()
+    with np.errstate(over="ignore"):
+        h64 = h.astype(np.float64) + gr.astype(np.float64) ** 2
+        step = np.float64(np.float32(lr)) * gr / (np.float64(np.float32(eps)) + np.sqrt(h64))
+    got = T.cpu().numpy().astype(np.float64)
+    # (sums of squares below 2^-126 lose bits of their own)
+    ok = np.abs(got - (th - step)) <= 2.0**-24 * np.abs(th - step) + 2.0**-21 * np.abs(step) + 1e-30
+    assert ok[h64 > 1e-37].all() or not np.isfinite(eps), (got, th - step)
+    assert np.isfinite(got).all()
+    if np.isinf(eps):
+        assert np.array_equal(got, th)
