@@ -258,14 +258,12 @@ int forward_one(gorila_ctx* c, char* base, const Plan& p, const gorila_params* p
         states_prep_kernel<<<tblocks + PREP_BLOCKS + wpn, 256, 0, st>>>(
             states, n, ftab, wv, tblocks, wj, wpn > 0 ? wpn : 1);
     }
-    GroupPtrs th{};
-    th.p[0] = theta;
     // forward-only calls compute in fp32 (bf16 parameters are exact in one plane)
     {
         StageTimer t(c, ST_CONV_FWD);
         launch_trunk_fwd(ftab, wv.frag, wv.planes, theta, n, fp(p.h3), c->cus, st);
     }
-    { StageTimer t(c, ST_FC1_FWD); *fc1_splits = launch_fc1_fwd(fp(p.h3), th, GroupPtrs16{}, 1, n, fp(p.fc1part), false, st); }
+    { StageTimer t(c, ST_FC1_FWD); *fc1_splits = launch_fc1_fwd_one(fp(p.h3), theta, n, fp(p.fc1part), c->cus, st); }
     return check_launch();
 }
 
@@ -694,7 +692,7 @@ int learner_steps(gorila_ctx* ctx, const gorila_params* params, int G, bool allo
     {
         StageTimer t(ctx, ST_FC1_BWD);
         head_blocks = launch_fc1_backward(dz4, on, w4b, G, h3, h4, a, coef, ell, b, A, dz3, grads_out, P,
-                                          at<float>(ctx, p.hpart), kp, sw, bf16, st);
+                                          at<float>(ctx, p.hpart), kp, ctx->cus, bf16, st);
     }
     {
         StageTimer t(ctx, ST_CONV_DGRAD);

@@ -119,7 +119,7 @@ __device__ __forceinline__ void tile_sequence(XLoad xload, bf16x8 (&w)[2][2][GP]
 }
 
 // GP planes of gradients and of weights: 3 for fp32 steps, 1 for bf16 ones
-// (gradients rounded to bf16).  dz3: `kp` partial planes [kp][rows][49][64] of
+// (gradients rounded to bf16).  dz3: `kp` partial planes [kp][rows][64][49] of
 // type T, added in order, the sum of more than one left as plane kp; dz2 [rows][81][64], dz1 [rows][400][32] of type O.
 template <int GP, class T, class O>
 __global__ __launch_bounds__(BD_THREADS) void bwd_data_kernel(
@@ -141,13 +141,15 @@ __global__ __launch_bounds__(BD_THREADS) void bwd_data_kernel(
     constexpr int T3 = (N3 + BD_THREADS - 1) / BD_THREADS, T2 = (N2 + BD_THREADS - 1) / BD_THREADS,
                   T1 = (N1 + BD_THREADS - 1) / BD_THREADS;
     f32x4 v3[T3], v2[T2], v1[T1];
+    // quad e of a sample of dz3 ([64][49]): channels 4 (e / 49) .. at pixel e % 49
+    auto at3 = [](int e, int c) { return (e / P3 * 4 + c) * P3 + e % P3; };
+    auto quad3 = [&](const T* z, int e) {
+        return f32x4{ldv(z + at3(e, 0)), ldv(z + at3(e, 1)), ldv(z + at3(e, 2)), ldv(z + at3(e, 3))};
+    };
     auto fetch = [&](int r) {
         const int et = opaque(tid);
 #pragma unroll
-        for (int k = 0; k < T3; ++k) {
-            const int e = min(et + k * BD_THREADS, N3 - 1);
-            v3[k] = ldq(dz3 + (int64_t)r * FLAT + 4 * e);
-        }
+        for (int k = 0; k < T3; ++k) v3[k] = quad3(dz3 + (int64_t)r * FLAT, min(et + k * BD_THREADS, N3 - 1));
 #pragma unroll
         for (int k = 0; k < T2; ++k)
             v2[k] = ld4(h2 + (int64_t)r * P2 * C2 + 4 * min(et + k * BD_THREADS, N2 - 1));
@@ -205,13 +207,14 @@ __global__ __launch_bounds__(BD_THREADS) void bwd_data_kernel(
                 if (e < N3) {
                     f32x4 v = v3[k];
                     if (kp > 1) {
-                        for (int s = 1; s < kp; ++s) v += ldq(dz3 + ((int64_t)s * rows + r) * FLAT + 4 * e);
-                        stq(dz3 + ((int64_t)kp * rows + r) * FLAT + 4 * e, v);
+                        for (int s = 1; s < kp; ++s) v += quad3(dz3 + ((int64_t)s * rows + r) * FLAT, e);
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) stv(dz3 + ((int64_t)kp * rows + r) * FLAT + at3(e, c), v[c]);
                     }
                     bf16x4 o[GP];
                     split4<GP>(v, o);
-                    const int p = e >> 4, y = p / H3, x = p - y * H3;
-                    const int off = bd_off((y + 2) * BD_W + x + 2, (y + 2) * H2 + x + 2, (e & 15) >> 1) + ((e & 1) << 3);
+                    const int cq = e / P3, p = e - cq * P3, y = p / H3, x = p - y * H3;
+                    const int off = bd_off((y + 2) * BD_W + x + 2, (y + 2) * H2 + x + 2, cq >> 1) + ((cq & 1) << 3);
 #pragma unroll
                     for (int pl = 0; pl < GP; ++pl) *(bf16x4*)(z3 + pl * BD_PLANE + off) = o[pl];
                 }

@@ -11,7 +11,7 @@
 //   h1, dz1 : [n][20][20][32]  pixel-major, channel-minor (NHWC)
 //   h2, dz2 : [n][9][9][64]    NHWC
 //   h3      : [n][64][49]      channel-major: the flatten order of the FC input
-//   dz3     : [n][49][64]      NHWC
+//   dz3     : [n][64][49]      flatten order, as h3
 //   h4, dz4 : [n][512]
 #pragma once
 #include <hip/hip_runtime.h>
@@ -686,8 +686,14 @@ constexpr int cmax(int a, int b) { return a > b ? a : b; }
 template <class T, class = void> struct MinWgs : std::integral_constant<int, 1> {};
 template <class T>
 struct MinWgs<T, std::void_t<decltype(T::MIN_WGS)>> : std::integral_constant<int, T::MIN_WGS> {};
+// A job of other than 256 threads names them: `static constexpr int THREADS`
+// (all jobs of a launch alike).
+template <class T, class = void> struct JobThreads : std::integral_constant<int, 256> {};
+template <class T>
+struct JobThreads<T, std::void_t<decltype(T::THREADS)>> : std::integral_constant<int, T::THREADS> {};
 template <class J1, class J2, class J3>
-__global__ __launch_bounds__(256, cmax(MinWgs<J1>::value, cmax(MinWgs<J2>::value, MinWgs<J3>::value)))
+__global__ __launch_bounds__(JobThreads<J1>::value,
+                             cmax(MinWgs<J1>::value, cmax(MinWgs<J2>::value, MinWgs<J3>::value)))
 void jobs_kernel(J1 a, J2 b, J3 c) {
     __shared__ __attribute__((aligned(16))) float smem[cmax(J1::SMEM, cmax(J2::SMEM, J3::SMEM))];
     int bid = blockIdx.x;
@@ -701,7 +707,7 @@ void jobs_kernel(J1 a, J2 b, J3 c) {
 template <class J1, class J2 = NoJob, class J3 = NoJob>
 inline void launch_jobs(hipStream_t st, const J1& a, const J2& b = J2{}, const J3& c = J3{}) {
     const int blocks = a.blocks() + b.blocks() + c.blocks();
-    if (blocks > 0) jobs_kernel<J1, J2, J3><<<blocks, 256, 0, st>>>(a, b, c);
+    if (blocks > 0) jobs_kernel<J1, J2, J3><<<blocks, JobThreads<J1>::value, 0, st>>>(a, b, c);
 }
 
 __device__ inline f32x4 zero4() { return f32x4{0.f, 0.f, 0.f, 0.f}; }

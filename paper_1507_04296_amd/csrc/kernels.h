@@ -228,6 +228,10 @@ void launch_conv3_fwd(const float* h2, const GroupPtrs& w3t, const GroupPtrs& th
 int launch_fc1_fwd(const float* h3, const GroupPtrs& theta, const GroupPtrs16& w4b, int groups,
                    int n, float* partial, bool bf16, hipStream_t st);
 
+// The same for a forward-only call of one fp32 set (larger ones on bf16 planes).
+int launch_fc1_fwd_one(const float* h3, const float* theta, int n, float* partial, int cus,
+                       hipStream_t st);
+
 // Head: Q values, epsilon-greedy actions, TD error / Huber loss / dLoss.
 // Each first finishes the FC-512 layer (splits in order, bias, ReLU).
 void launch_q_head(const float* fc1part, int splits, const float* theta, int n, int A, float* q,
@@ -247,14 +251,14 @@ void launch_td_head(const float* fc1part_online, const float* fc1part_target, in
 
 // Backward of `groups` learner groups of n rows each (group g: rows
 // g*n .. g*n+n-1 of every per-sample tensor, parameters of set g).
-// fc1: dz3 = [h3 > 0] W4^T dz4 (stored [b][p][o]) as kp partial planes, each
+// fc1: dz3 = [h3 > 0] W4^T dz4 (flatten order) as kp partial planes, each
 // groups * n rows long, dW4 and db4 into grads + g * grads_stride, and
 // row-block partials of dW5, db5 and the loss (returns row blocks per group).
 int launch_fc1_backward(const float* dz4, const GroupPtrs& theta, const GroupPtrs16& w4b,
                         int groups, const float* h3,
                         const float* h4, const int32_t* a, const float* coef, const float* ell,
                         int n, int A, float* dz3, float* grads, int64_t grads_stride,
-                        float* hpart, int kp, const SplitWs& sw, bool bf16, hipStream_t st);
+                        float* hpart, int kp, int cus, bool bf16, hipStream_t st);
 // dz2 [rows][81][64] and dz1 [rows][400][32] from kp planes of dz3 (bwd.hip),
 // whose fp32 sum is left as plane kp (kp > 1).
 // Outputs fp32, or (bf16) rounded to bf16, as the weight gradients read them;

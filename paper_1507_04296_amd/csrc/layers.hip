@@ -10,6 +10,7 @@
 // so activation quads are 16 contiguous bytes of an NHWC pixel.
 #include "common.h"
 #include "kernels.h"
+#include "fc1_planes.h"
 
 #include <type_traits>
 
@@ -307,9 +308,29 @@ int launch_fc1_fwd(const float* h3, const GroupPtrs& theta, const GroupPtrs16& w
     return splits;
 }
 
+// Up to 192 states the fp32 tiles are ahead: their 64-row tiles pad less and
+// 1024 smaller workgroups hide each other's loads (n = 1: 7.8 against 11.4 us,
+// 128: 8.8 against 12.5); from 200 on the planes are (200: 13.3 against 13.5 us,
+// 300: 14.1 against 17.4, 600: 16.7 against 28.4, 1024: 21.8 against 33.5).
+int launch_fc1_fwd_one(const float* h3, const float* theta, int n, float* partial, int cus,
+                       hipStream_t st) {
+    if (n <= 192) {
+        GroupPtrs th{};
+        th.p[0] = theta;
+        return launch_fc1_fwd(h3, th, GroupPtrs16{}, 1, n, partial, false, st);
+    }
+    // one round of one workgroup a unit (LDS)
+    const int tiles = (n + PgFwdJob::BM - 1) / PgFwdJob::BM * (HID / PgFwdJob::BN);
+    int splits = min(FC1_MAX_SPLITS, max(1, cus / tiles));
+    const int cps = (FC1_CHUNKS + splits - 1) / splits;
+    splits = (FC1_CHUNKS + cps - 1) / cps;
+    launch_jobs(st, PgFwdJob{h3, theta + OFF_W4, partial, n, splits, cps});
+    return splits;
+}
+
 // ---------------------------------------------------------------------------
 // fc1 data gradient: dz3 = [h3 > 0] * (W4^T dz4), rows b, cols k (3136 = 49
-// tiles), reduction o (16 chunks); dz3 is written as [b][p][o].
+// tiles), reduction o (16 chunks).
 // ---------------------------------------------------------------------------
 // B[col][k] = M[k][c0 + col] of a row-major [k][ld] matrix (RMAJ quads).
 // Reduction indices k >= kmax read row 0; ZERO makes them zeros (one operand
@@ -345,13 +366,11 @@ struct RowMajorR16 {  // RowMajorR<false> over a bf16 matrix
     }
 };
 
-// df is produced in the FC input's flatten order k = o*49 + p; dz3 is stored
-// pixel-major ([b][p][o], like the other activation gradients) so that the
-// conv3 backward kernels read it in 16-byte quads.
-struct Dz3NhwcStore {
+// dz3 keeps the FC input's flatten order k = o*49 + p, so it is stored as it is
+// computed (in [p][o] order every value of a row went to a line of its own).
+struct Dz3Store {
     static constexpr bool MASK = true;
-    float* dz3;       // fp32 dz3, or null
-    uint16_t* dz3h;   // bf16 dz3 (bf16 steps, one part), or null
+    float* dz3;
     const float* h3;
     int rows, r0, c0;
     __device__ float pre(int row, int col) const {
@@ -361,16 +380,13 @@ struct Dz3NhwcStore {
     __device__ void operator()(int row, int col, float v, float m) const {
         const int b = r0 + row;
         if (b >= rows) return;
-        const int k = c0 + col, o = k / P3, p = k - o * P3;
-        const float r = m > 0.0f ? v : 0.0f;
-        if (dz3h) stg(dz3h + (int64_t)b * FLAT + p * C3 + o, r);
-        else stg(dz3 + (int64_t)b * FLAT + p * C3 + o, r);
+        stg(dz3 + (int64_t)b * FLAT + c0 + col, m > 0.0f ? v : 0.0f);
     }
 };
 
 // kp > 1 cuts the reduction over the 512 hidden units into kp parts, each
 // writing its masked dz3 plane (the ReLU mask is linear in the parts).
-template <int BF, bool SPLIT = false>  // SPLIT as for Conv3FwdJob (kp == 1 only)
+template <int BF>  // bf16 steps: kp > 1 only
 struct Fc1DgradJob {
     const float* dz4;
     GroupPtrs theta;
@@ -378,41 +394,27 @@ struct Fc1DgradJob {
     const float* h3;
     float* dz3;
     int n, groups, kp;  // kp reduction parts, each writing its own dz3 plane
-    TailSplit ts;       // kp == 1 only
     static constexpr int PA = BF ? BF_GRAD : 0, PB = BF ? BF_WEIGHT : 0, CHUNKS = HID / BK;
     using SH = GemmShape<64, 64, KMAJ, RMAJ, PA, PB>;
     static constexpr int SMEM = SH::SMEM_FLOATS;
     __host__ __device__ int tiles() const { return ((n + 63) / 64) * (FLAT / 64); }
-    __host__ __device__ int blocks() const {
-        return SPLIT ? ts.blocks(tiles() * groups) : pad_xcd(tiles() * groups * kp);
-    }
+    __host__ __device__ int blocks() const { return pad_xcd(tiles() * groups * kp); }
     __device__ void run(int bid, float* smem) const {
-        int t, part = 0, kc0 = 0, kc1 = CHUNKS;  // HID is a whole number of chunks
-        SplitPiece sp;
-        if constexpr (SPLIT) {
-            if (!ts.map(bid, tiles() * groups, CHUNKS, t, kc0, kc1, sp)) return;
-        } else {
-            t = xcd_tile(bid, blocks());
-            if (t >= tiles() * groups * kp) return;
-            part = t / (tiles() * groups);
-            t -= part * tiles() * groups;
-            kc0 = part * CHUNKS / kp;
-            kc1 = (part + 1) * CHUNKS / kp;
-        }
+        int t = xcd_tile(bid, blocks());
+        if (t >= tiles() * groups * kp) return;
+        const int part = t / (tiles() * groups);
+        t -= part * tiles() * groups;
+        const int kc0 = part * CHUNKS / kp, kc1 = (part + 1) * CHUNKS / kp;  // HID is a whole number of chunks
         const int g = t / tiles();
         t -= g * tiles();
         const int mt = (n + 63) / 64;
         const int r0 = (t % mt) * 64, c0 = (t / mt) * 64;  // row tiles of one W4 column block adjacent
         const int64_t rows = (int64_t)g * n;
         RowMajorK la{dz4 + rows * HID, n, r0, HID};
-        const bool half = BF == 1 && kp == 1;  // dz3 as bf16
-        Dz3NhwcStore epi{half ? nullptr : dz3 + part * (int64_t)groups * n * FLAT + rows * FLAT,
-                         half ? (uint16_t*)dz3 + rows * FLAT : nullptr, h3 + rows * FLAT, n, r0, c0};
+        Dz3Store epi{dz3 + (part * (int64_t)groups * n + rows) * FLAT, h3 + rows * FLAT, n, r0, c0};
         // small-batch parts keep runtime bounds; whole tiles compile-time ones
         auto gemm = [&](auto& lb) {
-            if (SPLIT && sp.np > 1)
-                mfma_gemm<64, 64, 2, KMAJ, RMAJ, PA, PB>(smem, kc0, kc1, la, lb, epi, nullptr, sp);
-            else if (kp > 1)
+            if (BF > 0 || kp > 1)
                 mfma_gemm<64, 64, 2, KMAJ, RMAJ, PA, PB>(smem, kc0, kc1, la, lb, epi);
             else
                 mfma_gemm<64, 64, 2, KMAJ, RMAJ, PA, PB>(smem, 0, CHUNKS, la, lb, epi);
@@ -478,7 +480,7 @@ struct HeadPartialJob {
     static constexpr int SMEM = 4 * MAX_ACTIONS * 64;
     __host__ __device__ int blocks() const { return pad_xcd((HID / 64) * row_blocks * groups); }
     __device__ void run(int bid, float* smem) const {
-        if (bid >= (HID / 64) * row_blocks * groups) return;
+        if (bid >= (HID / 64) * row_blocks * groups || threadIdx.x >= 256) return;
         float (*sacc)[MAX_ACTIONS][64] = (float (*)[MAX_ACTIONS][64])smem;
         const int tid = threadIdx.x, kl = tid & 63, bq = tid >> 6;
         const int kt = bid % (HID / 64), gbb = bid / (HID / 64);
@@ -536,31 +538,44 @@ int launch_fc1_backward(const float* dz4, const GroupPtrs& theta, const GroupPtr
                         int groups, const float* h3,
                         const float* h4, const int32_t* a, const float* coef, const float* ell,
                         int n, int A, float* dz3, float* grads, int64_t grads_stride,
-                        float* hpart, int kp, const SplitWs& sw, bool bf16, hipStream_t st) {
+                        float* hpart, int kp, int cus, bool bf16, hipStream_t st) {
     if (n <= 0) return 0;
     const int rows = max(32, (n + HEAD_MAX_BLOCKS - 1) / HEAD_MAX_BLOCKS);
     const int row_blocks = (n + rows - 1) / rows;
     const HeadPartialJob hp{h4, a, coef, ell, hpart, n, A, rows, row_blocks, groups};
-    // the two GEMMs balance as one launch of equal tiles when their chunk
-    // counts agree (the batch rounds up to the 512 hidden units)
-    TailSplit ts;
-    const int wt = (HID / 64) * (FLAT / 64) * groups, dt = ((n + 63) / 64) * (FLAT / 64) * groups;
-    if (kp == 1 && (n + BK - 1) / BK == HID / BK)
-        ts = plan_split(sw.ws, sw.cnt, sw.cus, wt + dt, dt, HID / BK);
+    if (bf16 && kp == 1) {
+        // One plane: ahead of the fp32-staged tiles at every size measured (16
+        // learners x 64 rows 40.0 against 49.1 us, 8 x 128 30.0 against 39.9,
+        // 4 x 33 12.8 against 15.2).  The longer tiles go first: a weight
+        // gradient's chunk holds twice the products of a data gradient's.
+        const PgDgradJob<64, 64, 1, uint16_t> d{dz4, theta, w4b, h3, dz3, n, groups};
+        const PgWgradJob<128, 64, 1> w{dz4, h3, grads, grads_stride, n, groups};
+        if (2 * ((n + 31) / 32) > HID / 32) launch_jobs(st, w, d, hp);
+        else launch_jobs(st, d, w, hp);
+        return row_blocks;
+    }
+    if (!bf16 && kp == 1 && n > 320) {
+        // Three planes: 128-row tiles, one workgroup a unit, pay once the batch
+        // fills them (rows 256: 25.4 against 22.5 us, 320: 26.3 against 25.9,
+        // 352: 26.4 against 29.4, 512: 30.4 against 34.2, 1024: 60 against 72;
+        // four learners of 33 rows: 28.8 against 22.3).
+        launch_jobs(st, PgWgradJob<128, 128, 3>{dz4, h3, grads, grads_stride, n, groups},
+                    PgDgradJob<128, 128, 3, float>{dz4, theta, w4b, h3, dz3, n, groups}, hp);
+        return row_blocks;
+    }
     // Dispatch order: when the launch runs several rounds of workgroups per
     // compute unit and the data-gradient tiles are the longer ones (many
     // learner groups of a few rows each), those go first so that the short
     // weight-gradient tiles fill in behind them instead of trailing them.
-    // Otherwise (one round, or equal tiles whose last data-gradient tiles are
-    // split) the weight gradient goes first, which measured faster at batches
-    // 32 and 512.
-    const bool dgrad_first = (n + BK - 1) / BK < HID / BK / kp && wt + dt > 4 * sw.cus;
+    // Otherwise the weight gradient goes first, which measured faster at batch
+    // 32.
+    const int wt = (HID / 64) * (FLAT / 64) * groups, dt = ((n + 63) / 64) * (FLAT / 64) * groups;
+    const bool dgrad_first = (n + BK - 1) / BK < HID / BK / kp && wt + dt > 4 * cus;
     auto go = [&](auto bf) {
         constexpr int BF = decltype(bf)::value;
         const Fc1WgradJob<BF> w{dz4, h3, grads, grads_stride, n, groups};
-        const Fc1DgradJob<BF> d{dz4, theta, w4b, h3, dz3, n, groups, kp, ts};
+        const Fc1DgradJob<BF> d{dz4, theta, w4b, h3, dz3, n, groups, kp};
         if (dgrad_first) launch_jobs(st, d, w, hp);
-        else if (ts.tail) launch_jobs(st, w, Fc1DgradJob<BF, true>{dz4, theta, w4b, h3, dz3, n, groups, kp, ts}, hp);
         else launch_jobs(st, w, d, hp);
     };
     if (bf16) go(std::integral_constant<int, 1>{});

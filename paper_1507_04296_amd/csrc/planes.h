@@ -87,6 +87,20 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
+__device__ inline float ldv(const float* p) { return *p; }
+__device__ inline float ldv(const uint16_t* p) { return __uint_as_float((uint32_t)*p << 16); }
+__device__ inline void stv(float* p, float v) { *p = v; }
+__device__ inline void stv(uint16_t* p, float v) { *p = __builtin_bit_cast(uint16_t, (__bf16)v); }
+// The same quads at any element's address.
+typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t u16x4a __attribute__((ext_vector_type(4), aligned(2)));
+__device__ inline f32x4 ldqa(const float* p) { return *(const f32x4a*)p; }
+__device__ inline f32x4 ldqa(const uint16_t* p) {
+    const u16x4a v = *(const u16x4a*)p;
+    return f32x4{__uint_as_float((uint32_t)v[0] << 16), __uint_as_float((uint32_t)v[1] << 16),
+                 __uint_as_float((uint32_t)v[2] << 16), __uint_as_float((uint32_t)v[3] << 16)};
+}
+
 // Products of R row tiles with the column tiles J0 .. J0 + C - 1: the leading
 // ones into hi, the others into lo.  Each plane pair is a round of R C
 // independent instructions; the scheduling barriers keep the rounds apart (the

@@ -81,7 +81,8 @@ template <int GP>
 constexpr int WG_LDS = 2 * GP * (Wg2::A_PLANE + Wg2::X_PLANE);
 static_assert(Wg3::A_PLANE + Wg3::X_PLANE <= Wg2::A_PLANE + Wg2::X_PLANE, "conv2 is the larger");
 
-// One workgroup: samples [b0, b1) of one group.  dz: [b][PIX][64]; x: h1 [b][400][32] or h2 [b][81][64]; part
+// One workgroup: samples [b0, b1) of one group.  dz: dz2 [b][81][64]
+// or dz3 [b][64][49]; x: h1 [b][400][32] or h2 [b][81][64]; part
 // [64][LD]; bias [64] (slice 0 only, else null).
 template <class G, int GP, class T>
 __device__ __forceinline__ void wgrad_run(char* lds, int slice, int b0, int b1, const T* __restrict__ dz,
@@ -111,15 +112,31 @@ __device__ __forceinline__ void wgrad_run(char* lds, int slice, int b0, int b1, 
         aok[e] = m >= 0;
         apix[e] = (m >= 0 ? m : 0) * 64 + cq * 4;
     }
+    // dz2 is [81][64]: quad e is four channels of pixel e; dz3 is [64][49]: quad e
+    // is the set's four pixels of channel e, one vector (a set's pixels follow
+    // one another; a padding pixel reads what follows, the last three of the last
+    // channel one value early)
+    if constexpr (!CONV2) {
+        const int p0 = max(0, set_pixel<false>(set, 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) apix[e] = (cq * 4 + e) * P3 + p0;
+    }
+    const bool early = !CONV2 && apix[3] + 3 >= FLAT;
+    if (early) apix[3] -= 1;
     f32x4 va[4], vx[TX], bsum = {};
     auto fetch_a = [&](int b) {
         const T* const z = dz + (int64_t)b * G::PIX * 64;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) va[e] = ldq(z + apix[e]);
+        for (int e = 0; e < 4; ++e) {
+            if constexpr (CONV2) va[e] = ldq(z + apix[e]);
+            else va[e] = ldqa(z + apix[e]);
+        }
+        if (early) va[3] = f32x4{va[3][1], va[3][2], va[3][3], 0.0f};
     };
     auto stage_a = [&](char* buf, int c) {  // channel c of the four
-        const f32x4 v{aok[0] ? va[0][c] : 0.f, aok[1] ? va[1][c] : 0.f, aok[2] ? va[2][c] : 0.f,
-                      aok[3] ? va[3][c] : 0.f};
+        f32x4 v = va[c];
+        if constexpr (CONV2) v = f32x4{va[0][c], va[1][c], va[2][c], va[3][c]};
+        v = f32x4{aok[0] ? v[0] : 0.f, aok[1] ? v[1] : 0.f, aok[2] ? v[2] : 0.f, aok[3] ? v[3] : 0.f};
         bsum[c] += (v[0] + v[1]) + (v[2] + v[3]);
         bf16x4 o[GP];
         split4<GP>(v, o);
