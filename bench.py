@@ -44,17 +44,21 @@ def step_flops_per_transition(A: int) -> int:
     return 2 * (2 * fwd + bwd)
 
 
-MFMA_STAGES = ("conv1_fwd", "conv2_fwd", "conv3_fwd", "fc1_fwd", "fc1_bwd", "conv_dgrad",
-               "conv_wgrad", "conv1_wgrad")
+MFMA_STAGES = ("conv1_fwd", "conv2_fwd", "conv3_fwd", "fc1_fwd", "conv_fwd", "fc1_bwd",
+               "conv_dgrad", "conv_wgrad", "conv1_wgrad")
 
 
-def stage_flops(stage: str, B: int, A: int) -> float:
+def stage_flops(stage: str, B: int, A: int, stages=()) -> float:
     """Algorithmic FLOPs of one launch of a stage of the learner step at batch B
     (fc1_bwd holds a data gradient and a weight gradient, conv_dgrad and
-    conv_wgrad those of conv2 and conv3)."""
+    conv_wgrad those of conv2 and conv3).  Where the step has a conv_fwd stage,
+    that is the target rows' conv1 to conv3, and conv1_fwd to conv3_fwd hold the
+    learner's rows alone."""
     two = 2 * B  # online + target rows in the forward stages
+    conv = B if "conv_fwd" in stages else two
     table = {
-        "conv1_fwd": two * MAC_CONV1, "conv2_fwd": two * MAC_CONV2, "conv3_fwd": two * MAC_CONV3,
+        "conv1_fwd": conv * MAC_CONV1, "conv2_fwd": conv * MAC_CONV2, "conv3_fwd": conv * MAC_CONV3,
+        "conv_fwd": B * (MAC_CONV1 + MAC_CONV2 + MAC_CONV3),
         "fc1_fwd": two * MAC_FC1, "head": two * 512 * A + B * 512,
         "fc1_bwd": 2 * B * MAC_FC1 + B * 512, "conv_dgrad": B * (MAC_CONV3 + MAC_CONV2),
         "conv_wgrad": B * (MAC_CONV3 + MAC_CONV2), "conv1_wgrad": B * MAC_CONV1,
@@ -571,10 +575,10 @@ def main():
     r = run_learner(torch, g, datagen, B, A, seed, args.steps, args.warmup)
     fpt = step_flops_per_transition(A)
     step_tflops = B * fpt / (r["ms_per_step"] * 1e-3) / 1e12
-    dom_flops = stage_flops(r["dominant"], B, A)
+    dom_flops = stage_flops(r["dominant"], B, A, r["prof"])
     dom_tflops = dom_flops / (r["dominant_ms"] * 1e-3) / 1e12
     stages = {k: {"ms": round(v[0] / max(v[1], 1), 4),
-                  "tflops": round(stage_flops(k, B, A) / (v[0] / max(v[1], 1) * 1e-3) / 1e12, 2)}
+                  "tflops": round(stage_flops(k, B, A, r["prof"]) / (v[0] / max(v[1], 1) * 1e-3) / 1e12, 2)}
               for k, v in r["prof"].items()}
     out = {
         "metric": "learner transitions/sec (DQN fwd+bwd) and % MFMA peak at batch 32/512",

@@ -113,7 +113,7 @@ constexpr Plan make_plan(int64_t fwd_rows, int64_t bwd_rows, int A, int online =
     p.term = take((size_t)B);
     p.theta32_stride = up(4 * (size_t)param_count(A));
     p.theta32 = take(p.theta32_stride * (size_t)widened);
-    p.frag = B ? o : take(FRAG_PLANES * FRAG_BYTES);  // forward-only calls
+    p.frag = take(FRAG_PLANES * FRAG_BYTES);  // one set: a forward-only call's, a learner step's target
     p.w2t = B ? take(W2T_BYTES * (size_t)(online + 1)) : o;
     p.w3t = B ? take(W3T_BYTES * (size_t)(online + 1)) : o;
     p.fragd = B ? take(FRAG_PLANES * FRAGD_BYTES * (size_t)online) : o;
@@ -139,6 +139,24 @@ constexpr Plan make_plan(int64_t fwd_rows, int64_t bwd_rows, int A, int online =
     p.split = B ? take(4 * (size_t)SPLIT_MAX_SLOTS * SPLIT_TILE_FLOATS) : o;
     p.total = o;
     return p;
+}
+
+// Whether a learner step takes conv1 to conv3 of its target rows as one launch
+// (trunk.hip) and only the learners' rows layer by layer.  The target's h1 and
+// h2 are read by nothing else, and its Q values enter through a maximum and a
+// clipped difference, both continuous; the learners' own forward pass keeps its
+// order of sums, because a hidden unit near zero that changes sides changes the
+// gradient by more than any rounding.  The launch walks samples in rounds of
+// one a compute unit, 18 us (bf16: 12 us) each, so it pays where the rounds are
+// full.  Whole step, all rows layer by layer -> this, us, at `rows` B:
+//   fp32: 256 193 -> 185, 300 225 -> 233, 420 275 -> 275, 512 300 -> 297, 620 370 -> 359,
+//         768 447 -> 412, 1030 608 -> 573, 2001 1047 -> 966; 128 126 -> 141
+//   bf16: 256 165 -> 170, 512 182 -> 180, 600 223 -> 226, 768 278 -> 264, 825 307 -> 320,
+//         896 338 -> 338, 1000 306 -> 285, 1024 353 -> 335
+bool target_in_one_launch(int64_t rows, int cus, bool bf16) {
+    const int64_t u = cus > 0 ? cus : 1, rounds = (rows + u - 1) / u;
+    if (bf16) return rounds >= 2 && 10 * rows >= 9 * u * rounds;
+    return rounds >= 3 ? 10 * rows >= 8 * u * rounds : 10 * rows >= 9 * u * rounds;
 }
 
 template <class T>
@@ -606,12 +624,19 @@ int learner_steps(gorila_ctx* ctx, const gorila_params* params, int G, bool allo
     const float* theta[MAX_LEARNER_GROUPS];
     for (int g = 0; g < G; ++g) theta[g] = fp32_params(ctx, p, &params[g], widen, n_widen);
     const float* theta_t = fp32_params(ctx, p, target_params, widen, n_widen);
+    // The target's rows, whose h1 and h2 nothing else reads, can go through
+    // conv1 to conv3 as one launch
+    const bool target_trunk = target_in_one_launch(B, ctx->cus, bf16);
     WeightViews wv[MAX_NETS];
     for (int g = 0; g <= G; ++g) {
         wv[g].theta = g < G ? theta[g] : theta_t;
+        wv[g].planes = bf16 ? 1 : FRAG_PLANES;
+        if (g == G && target_trunk) {
+            wv[g].frag = at<uint16_t>(ctx, p.frag);
+            continue;
+        }
         wv[g].w2t = at<float>(ctx, p.w2t + (size_t)g * W2T_BYTES);
         wv[g].w3t = at<float>(ctx, p.w3t + (size_t)g * W3T_BYTES);
-        wv[g].planes = bf16 ? 1 : FRAG_PLANES;
         if (g < G) wv[g].fragd = at<uint16_t>(ctx, p.fragd + (size_t)g * FRAG_PLANES * FRAGD_BYTES);
     }
     // bf16 steps read W4 in place (the fc1 kernels widen it as they load), so
@@ -654,10 +679,19 @@ int learner_steps(gorila_ctx* ctx, const gorila_params* params, int G, bool allo
     float* h3 = at<float>(ctx, p.h3);
     float* h4 = at<float>(ctx, p.h4);
     float* fc1part = at<float>(ctx, p.fc1part);
-    const SplitWs sw = split_ws(ctx, p);
-    { StageTimer t(ctx, ST_CONV1_FWD); launch_conv1_fwd(ftab, th, 2 * G, b, h1, bf16, st); }
-    { StageTimer t(ctx, ST_CONV2_FWD); launch_conv2_fwd(h1, w2t, th, 2 * G, b, h2, sw, bf16, st); }
-    { StageTimer t(ctx, ST_CONV3_FWD); launch_conv3_fwd(h2, w3t, th, 2 * G, b, h3, sw, bf16, st); }
+    if (target_trunk) {
+        StageTimer t(ctx, ST_CONV_FWD);
+        launch_trunk_fwd(ftab + 4 * (int64_t)B, wv[G].frag, wv[G].planes, theta_t, B, h3 + (int64_t)B * FLAT,
+                         ctx->cus, st);
+    }
+    const int cg = target_trunk ? G : 2 * G;  // forward groups taken layer by layer
+    // A launch over both halves splits none of the learners' tiles at these sizes
+    // (more tiles than units, split ones last), so these run whole: the same sums.
+    SplitWs sw = split_ws(ctx, p);
+    if (target_trunk) sw.ws = nullptr;
+    { StageTimer t(ctx, ST_CONV1_FWD); launch_conv1_fwd(ftab, th, cg, b, h1, bf16, st); }
+    { StageTimer t(ctx, ST_CONV2_FWD); launch_conv2_fwd(h1, w2t, th, cg, b, h2, sw, bf16, st); }
+    { StageTimer t(ctx, ST_CONV3_FWD); launch_conv3_fwd(h2, w3t, th, cg, b, h3, sw, bf16, st); }
     int S = 0;
     { StageTimer t(ctx, ST_FC1_FWD); S = launch_fc1_fwd(h3, th, w4f, 2 * G, b, fc1part, bf16, st); }
 

@@ -1,4 +1,5 @@
-"""The one-launch convolution stack of the forward-only calls (Section 5.1).
+"""The one-launch convolution stack (Section 5.1): forward-only calls, and the
+target's rows of a learner step whose rounds of 256 are nearly full.
 
 Its workgroups walk samples n, n + 256, ...: sizes around one and two rounds of
 256, and the smallest.  Sums are of exact products in fp32; the bound on Q is
@@ -12,6 +13,7 @@ import pytest
 torch = pytest.importorskip("torch")
 
 import oracle
+import parity
 import paper_1507_04296_amd as g
 from paper_1507_04296_amd import datagen
 
@@ -47,3 +49,37 @@ def test_q_of_every_round(n, bf16):
         g.gorila_act_noalloc(g.Context(0, A), t, A, torch.from_numpy(states).to(dev), 0.0, 3, acts, q2)
         assert torch.equal(q, q2) and np.array_equal(acts.cpu().numpy(), got.argmax(1))
     ctx.close()
+
+
+# the rows where the choice changes with 256 units, and bf16's first round
+@pytest.mark.parametrize("G,b,bf16", [(1, 230, False), (1, 231, False), (7, 33, False),
+                                      (1, 460, False), (1, 461, False), (1, 615, False),
+                                      (2, 128, True), (4, 115, True), (4, 116, True)])
+def test_target_rows(G, b, bf16):
+    """Against the fp64 oracle, at the bars of every learner test."""
+    print(f"[gpu-case] target rows G={G} b={b} bf16={bf16}", flush=True)
+    A = 18
+    inp = datagen.grouped_inputs(7700 + G * b, G, b, A)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    inp.s2[0, :3] = 0          # blank channels, as at an episode start
+    rep = g.Replay.stacked(t(inp.s), t(inp.s2), t(inp.a), t(inp.r), t(inp.term))
+    idx = np.arange(G * b, dtype=np.int64)
+    th64 = [datagen.bf16_bits_to_f64(x) for x in inp.theta_bf16]
+    tg64 = datagen.bf16_bits_to_f64(inp.target_bf16)
+    ctx = g.Context(b, A, groups=G, dtype=g.GORILA_BF16 if bf16 else g.GORILA_F32)
+    if bf16:
+        th, tg = t(inp.theta_bf16.view(np.int16)), t(inp.target_bf16.view(np.int16))
+    else:
+        th, tg = [t(x.astype(np.float32)) for x in th64], t(tg64.astype(np.float32))
+    grads, loss = g.learner_step_grouped(ctx, th, tg, A, rep, t(idx), inp.gamma, 1.0)
+    ctx.check()
+    ctx.close()
+    got, got_l = grads.cpu().numpy().reshape(G, -1), loss.cpu().numpy()
+    net = oracle.Net(n_actions=A)
+    for i, x in enumerate(th64):
+        rows = idx[i * b:(i + 1) * b]
+        ref = oracle.learner_step(net, x, tg64, inp.s[rows], inp.s2[rows], inp.a[rows], inp.r[rows],
+                                  inp.term[rows], inp.gamma, 1.0)
+        parity.assert_grads_close(got[i], ref["grads"], A,
+                                  parity.GRAD_TOL_BF16 if bf16 else parity.GRAD_TOL)
+        assert abs(got_l[i] - ref["loss"]) <= parity.LOSS_TOL * abs(ref["loss"])
