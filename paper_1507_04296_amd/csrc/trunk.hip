@@ -23,6 +23,11 @@
 // Here an activation is stored to LDS once and the weights stream from the
 // XCD's L2 straight into registers in operand order (prep_weights_part), 456
 // KB a sample with three planes.
+//
+// Measured against the three layer launches: 1024 fp32 states 106 -> 70 us, one
+// state 27 -> 17 us.  A sample takes 33.5 thousand cycles, 21.1 of them matrix
+// instructions (six plane products); the rest is the epilogues' splits and
+// stores and the waits at the layers' barriers, with one workgroup a unit (LDS).
 #include "common.h"
 #include "kernels.h"
 #include "planes.h"
