@@ -270,7 +270,7 @@ __global__ __launch_bounds__(BD_THREADS) void bwd_data_kernel(
             // a wave hands channel tile 1 - kh to its partner and finishes tile kh
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
-                const f32x4 a = hi[0][j] + lo[0][j], b = hi[1][j] + lo[1][j];
+                const f32x4 a = plane_sum<GP>(hi[0][j], lo[0][j]), b = plane_sum<GP>(hi[1][j], lo[1][j]);
                 xch[(wave * 3 + j) * 64 + lane] = kh ? a : b;
                 hi[0][j] = kh ? b : a;
             }
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(BD_THREADS) void bwd_data_kernel(
                             const unsigned b = m1[p * 8 + i * 4 + (c0 >> 2)];
                             f32x4 v;
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) v[e] = b >> e & 1u ? hi[i][j][e] + lo[i][j][e] : 0.0f;
+                            for (int e = 0; e < 4; ++e) v[e] = b >> e & 1u ? plane_sum<GP>(hi[i][j][e], lo[i][j][e]) : 0.0f;
                             stq(out + p * C1 + i * 16 + c0, v);
                         }
                     }

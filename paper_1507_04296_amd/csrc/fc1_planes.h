@@ -189,8 +189,8 @@ __device__ __forceinline__ void pg_tile(char* lds, int c0, int c1, OA& a, OB& b,
         for (int e = 0; e < 4; ++e) {
             const int row = pg_row<BM>((rg * RT + i) * 16 + 4 * (el >> 4) + e);
             epi(row, cg * 64 + 4 * (el & 15),
-                f32x4{hi[i][0][e] + lo[i][0][e], hi[i][1][e] + lo[i][1][e], hi[i][2][e] + lo[i][2][e],
-                      hi[i][3][e] + lo[i][3][e]});
+                plane_sum<P>(f32x4{hi[i][0][e], hi[i][1][e], hi[i][2][e], hi[i][3][e]},
+                          f32x4{lo[i][0][e], lo[i][1][e], lo[i][2][e], lo[i][3][e]}));
         }
 }
 template <int BM, int BN, int P>

@@ -36,6 +36,22 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// The sum of the leading products' accumulator and the others' (of P planes an
+// operand at most).  An infinite operand is (inf, NaN, NaN) in planes, so its
+// leading products are infinite, or NaN against a zero, as the fp32
+// instruction's are, but the others are NaN or infinite: they are held within
+// the finite numbers (a NaN becomes the lowest), so that the leading sum decides
+// (a ReLU would turn the NaN into zero).
+template <int P>
+__device__ __forceinline__ float plane_sum(float hi, float lo) {
+    return hi + (P > 1 ? __builtin_amdgcn_fmed3f(lo, -0x1.fffffep127f, 0x1.fffffep127f) : lo);
+}
+template <int P>
+__device__ __forceinline__ f32x4 plane_sum(f32x4 hi, f32x4 lo) {
+    return f32x4{plane_sum<P>(hi[0], lo[0]), plane_sum<P>(hi[1], lo[1]), plane_sum<P>(hi[2], lo[2]),
+                 plane_sum<P>(hi[3], lo[3])};
+}
+
 // A copy of a value that the compiler cannot see through: what derives from
 // it is computed where it is used, per sample, instead of being kept in
 // registers over the whole row loop.

@@ -220,7 +220,7 @@ __global__ __launch_bounds__(TR_THREADS) void trunk_fwd_kernel(
                     f32x4 v;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const float s = WP > 1 ? hi[k][e] + lo[k][e] : hi[k][e];
+                        const float s = WP > 1 ? plane_sum<WP>(hi[k][e], lo[k][e]) : hi[k][e];
                         v[e] = fmaxf(s * (1.0f / 255.0f) + bias[e], 0.0f);
                     }
                     bf16x4 o[AP];
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(TR_THREADS) void trunk_fwd_kernel(
             // partner and finishes channel tile kh
 #pragma unroll
             for (int j = 0; j < TR_T2; ++j) {
-                const f32x4 a = hi[0][j] + lo[0][j], b = hi[1][j] + lo[1][j];
+                const f32x4 a = plane_sum<AP>(hi[0][j], lo[0][j]), b = plane_sum<AP>(hi[1][j], lo[1][j]);
                 xch2[(wave * TR_T2 + j) * 64 + lane] = kh ? a : b;
                 hi[0][j] = kh ? b : a;
             }
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(TR_THREADS) void trunk_fwd_kernel(
             wload(wf1, 2, 1, 1);
 #pragma unroll
             for (int j = 0; j < TR_T3; ++j) {
-                const f32x4 a = hi[0][j] + lo[0][j], b = hi[1][j] + lo[1][j];
+                const f32x4 a = plane_sum<AP>(hi[0][j], lo[0][j]), b = plane_sum<AP>(hi[1][j], lo[1][j]);
                 xch3[(wave * TR_T3 + j) * 64 + lane] = kh ? a : b;
                 hi[0][j] = kh ? b : a;
             }

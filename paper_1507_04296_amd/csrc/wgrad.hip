@@ -269,7 +269,7 @@ __device__ __forceinline__ void wgrad_run(char* lds, int slice, int b0, int b1, 
             const int c = CONV2 ? (tu * 4 + tv + j) * C1 + slice * 16 + (lane & 15)
                                 : (slice * 3 + j) * C2 + ng * 16 + (lane & 15);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) part[(o + 4 * e) * G::LD + c] = hi[i][j][e] + lo[i][j][e];
+            for (int e = 0; e < 4; ++e) part[(o + 4 * e) * G::LD + c] = plane_sum<GP>(hi[i][j][e], lo[i][j][e]);
         }
     if (bias) {
         // 32 threads hold each channel quad; the buffers are free

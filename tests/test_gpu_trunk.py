@@ -83,3 +83,42 @@ def test_target_rows(G, b, bf16):
         parity.assert_grads_close(got[i], ref["grads"], A,
                                   parity.GRAD_TOL_BF16 if bf16 else parity.GRAD_TOL)
         assert abs(got_l[i] - ref["loss"]) <= parity.LOSS_TOL * abs(ref["loss"])
+
+
+# One infinite weight of conv2, conv3 and the FC layer (fp32 tiles, plane tiles):
+# Q is infinite where the reference's is, NaN or finite where that is.  The
+# reference adds in fp64 and takes a ReLU's NaN as zero, as the kernels do.
+@pytest.mark.parametrize("n", [3, 257])
+@pytest.mark.parametrize("layer", ["conv2", "conv3", "fc1"])
+def test_infinite_weight(layer, n):
+    A = 5
+    inp = datagen.actor_inputs(17 + n, n, A)
+    theta = inp.theta.copy()
+    at = {"conv2": 8224 + 3 * 512 + 37, "conv3": 41056 + 5 * 576 + 100, "fc1": 77984 + 9 * 3136 + 1300}[layer]
+    theta[at] = np.inf
+    states = inp.states[:n]
+    F = torch.nn.functional
+    p = torch.from_numpy(theta.astype(np.float64))
+    cut = lambda o, *s: p[o:o + int(np.prod(s))].view(*s)
+    relu = lambda x: torch.nan_to_num(x, nan=0.0, posinf=np.inf, neginf=-np.inf).clamp_min(0.0)
+    x = torch.from_numpy(states).double() / 255.0
+    conv = lambda x, o, c, ci, k, s: relu(
+        (F.unfold(x, k, stride=s).transpose(1, 2) @ cut(o, c, ci * k * k).T).transpose(1, 2)
+        + cut(o + c * ci * k * k, c)[None, :, None])
+    h1 = conv(x, 0, 32, 4, 8, 4).view(n, 32, 20, 20)
+    h2 = conv(h1, 8224, 64, 32, 4, 2).view(n, 64, 9, 9)
+    h3 = conv(h2, 41056, 64, 64, 3, 1).reshape(n, 3136)
+    h4 = relu(h3 @ cut(77984, 512, 3136).T + cut(1683616, 512))
+    ref = (h4 @ cut(1684128, A, 512).T + cut(1684128 + A * 512, A)).numpy()
+    ctx = g.Context((n + 1) // 2, A)
+    got = g.q_forward(ctx, torch.from_numpy(theta).cuda(), A, torch.from_numpy(states).cuda()).cpu().numpy()
+    ctx.check()
+    ctx.close()
+    assert np.array_equal(np.isfinite(got), np.isfinite(ref))
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    fin = np.isfinite(ref)
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    if fin.any():
+        assert np.abs(got[fin] - ref[fin]).max() <= 2e-6 * np.abs(ref[fin]).max()
+    if layer == "fc1":
+        assert np.isinf(ref).any()
