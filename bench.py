@@ -53,15 +53,16 @@ def stage_flops(stage: str, B: int, A: int, stages=()) -> float:
     (fc1_bwd holds a data gradient and a weight gradient, conv_dgrad and
     conv_wgrad those of conv2 and conv3).  Where the step has a conv_fwd stage,
     that is the target rows' conv1 to conv3, and conv1_fwd to conv3_fwd hold the
-    learner's rows alone."""
+    learner's rows alone; without a conv1_wgrad stage conv_wgrad holds conv1's too."""
     two = 2 * B  # online + target rows in the forward stages
     conv = B if "conv_fwd" in stages else two
+    wgrad1 = MAC_CONV1 if "conv_wgrad" in stages and "conv1_wgrad" not in stages else 0
     table = {
         "conv1_fwd": conv * MAC_CONV1, "conv2_fwd": conv * MAC_CONV2, "conv3_fwd": conv * MAC_CONV3,
         "conv_fwd": B * (MAC_CONV1 + MAC_CONV2 + MAC_CONV3),
         "fc1_fwd": two * MAC_FC1, "head": two * 512 * A + B * 512,
         "fc1_bwd": 2 * B * MAC_FC1 + B * 512, "conv_dgrad": B * (MAC_CONV3 + MAC_CONV2),
-        "conv_wgrad": B * (MAC_CONV3 + MAC_CONV2), "conv1_wgrad": B * MAC_CONV1,
+        "conv_wgrad": B * (MAC_CONV3 + MAC_CONV2 + wgrad1), "conv1_wgrad": B * MAC_CONV1,
     }
     return 2.0 * table.get(stage, 0)
 

@@ -734,12 +734,12 @@ int learner_steps(gorila_ctx* ctx, const gorila_params* params, int G, bool allo
     }
     {
         StageTimer t(ctx, ST_CONV_WGRAD);
-        launch_conv_wgrad(kp > 1 ? dz3 + (int64_t)kp * B * FLAT : dz3, bf16 && kp == 1, h2, dz2, h1, G, b,
+        s1 = launch_conv_wgrad(kp > 1 ? dz3 + (int64_t)kp * B * FLAT : dz3, bf16 && kp == 1, h2, dz2, h1, G, b,
                           at<float>(ctx, p.part3), at<float>(ctx, p.part2),
-                          bpart + 2 * BIAS_PART_STRIDE, bpart + BIAS_PART_STRIDE, &s3, &s2, bf16,
-                          ctx->cus, st);
+                          bpart + 2 * BIAS_PART_STRIDE, bpart + BIAS_PART_STRIDE, &s3, &s2, dz1, ftab,
+                          at<uint8_t>(ctx, p.zero), at<float>(ctx, p.part1), bpart, bf16, ctx->cus, st);
     }
-    {
+    if (!s1) {
         StageTimer t(ctx, ST_CONV1_WGRAD);
         launch_conv1_wgrad(dz1, ftab, at<uint8_t>(ctx, p.zero), G, b, at<float>(ctx, p.part1), bpart,
                            CONV1_WG_MAX_SPLITS, &s1, bf16, st);

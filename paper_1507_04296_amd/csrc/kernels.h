@@ -267,10 +267,14 @@ void launch_bwd_data(float* dz3, int kp, const float* h2, const float* h1,
                      const GroupPtrs16& frags, int groups, int n, float* dz2, float* dz1, bool bf16,
                      int cus, hipStream_t st);
 // Split partials of dW3 / db3 and dW2 / db2 in one launch (wgrad.hip; dz3 and
-// dz2 as above, dz3 one plane); *s3, *s2: splits per group.
-void launch_conv_wgrad(const float* dz3, bool dz3_bf16, const float* h2, const float* dz2, const float* h1,
-                       int groups, int n, float* part3, float* part2, float* bias3, float* bias2,
-                       int* s3, int* s2, bool bf16, int cus, hipStream_t st);
+// dz2 as above, dz3 one plane); *s3, *s2: splits per group.  Small fp32 steps'
+// launch takes conv1's partials (dz1 .. bias1 as launch_conv1_wgrad) too and
+// returns their splits per group; 0: they are still to be formed.
+int launch_conv_wgrad(const float* dz3, bool dz3_bf16, const float* h2, const float* dz2, const float* h1,
+                      int groups, int n, float* part3, float* part2, float* bias3, float* bias2,
+                      int* s3, int* s2, const float* dz1, const uint8_t* const* ftab,
+                      const uint8_t* zero_frame, float* part1, float* bias1, bool bf16, int cus,
+                      hipStream_t st);
 // ftab: [groups * n][4] frame pointers of the online states (null: zero-filled);
 // zero_frame: FRAME_BYTES of zeros, read in place of a null frame; dz1 as
 // launch_bwd_data wrote it (bf16 bit patterns when bf16).

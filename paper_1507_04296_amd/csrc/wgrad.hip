@@ -23,6 +23,7 @@
 // pixel sets did not shorten it, nor did spreading the staging over the products.
 // Times are given with the data gradients (bwd.hip).
 #include "common.h"
+#include "conv1_wgrad.h"
 #include "kernels.h"
 #include "planes.h"
 
@@ -284,18 +285,39 @@ __device__ __forceinline__ void wgrad_run(char* lds, int slice, int b0, int b1, 
     }
 }
 
-template <int GP, class T3, class T2>
+// conv1's part of a launch of all three layers: `blocks` workgroups a group (0: none).
+struct C1wPart {
+    int blocks = 0, splits = 0;
+    const float* dz1 = nullptr;
+    const uint8_t* const* ftab = nullptr;
+    const uint8_t* zero_frame = nullptr;
+    float* part = nullptr;
+    float* bias = nullptr;
+};
+
+template <int GP, bool WITH1, class T3, class T2>
 __global__ __launch_bounds__(WG_THREADS) void conv_wgrad_kernel(
     const T3* __restrict__ dz3, const float* __restrict__ h2, const T2* __restrict__ dz2,
     const float* __restrict__ h1, int groups, int n, int s3, int s2, float* __restrict__ part3,
-    float* __restrict__ part2, float* __restrict__ bias3, float* __restrict__ bias2) {
+    float* __restrict__ part2, float* __restrict__ bias3, float* __restrict__ bias2, C1wPart c1) {
+    static_assert(!WITH1 || (C1W_LDS <= WG_LDS<GP> && WG_THREADS == 64 * C1W_WAVES), "conv1's workgroups fit");
     __shared__ __attribute__((aligned(16))) char lds[WG_LDS<GP>];
+    int bid = blockIdx.x;
+    if constexpr (WITH1) {
+        const int n1 = c1.blocks * groups;  // a multiple of 16: the others keep their XCDs
+        if (bid < n1) {
+            conv1_wgrad_run<GP>(lds, bid % c1.blocks, bid / c1.blocks, c1.dz1, c1.ftab, c1.zero_frame, n,
+                                c1.splits, c1.part, c1.bias);
+            return;
+        }
+        bid -= n1;
+    }
     // conv2 first (its samples cost more); the slices of one range, which read
     // the same dz, are neighbours and so share an XCD's L2
     const int n2 = Wg2::SLICES * s2 * groups, n3 = Wg3::SLICES * s3 * groups, pad2 = pad_xcd(n2);
     int t;
-    if ((int)blockIdx.x < pad2) {
-        t = xcd_tile(blockIdx.x, pad2);
+    if (bid < pad2) {
+        t = xcd_tile(bid, pad2);
         if (t >= n2) return;
         const int slice = t % Wg2::SLICES, gs = t / Wg2::SLICES, g = gs / s2, ks = gs - g * s2;
         const int64_t row = (int64_t)g * n;
@@ -303,7 +325,7 @@ __global__ __launch_bounds__(WG_THREADS) void conv_wgrad_kernel(
                            dz2 + row * P2 * C2, h1 + row * P1 * C1,
                            part2 + (int64_t)gs * C2 * Wg2::LD, slice == 0 ? bias2 + gs * 64 : nullptr);
     } else {
-        t = xcd_tile(blockIdx.x - pad2, pad_xcd(n3));
+        t = xcd_tile(bid - pad2, pad_xcd(n3));
         if (t >= n3) return;
         const int slice = t % Wg3::SLICES, gs = t / Wg3::SLICES, g = gs / s3, ks = gs - g * s3;
         const int64_t row = (int64_t)g * n;
@@ -313,22 +335,15 @@ __global__ __launch_bounds__(WG_THREADS) void conv_wgrad_kernel(
     }
 }
 
-void launch_conv_wgrad(const float* dz3, bool dz3_bf16, const float* h2, const float* dz2, const float* h1,
-                       int groups, int n, float* part3, float* part2, float* bias3, float* bias2,
-                       int* s3, int* s2, bool bf16, int cus, hipStream_t st) {
-    *s3 = *s2 = 0;
-    if (n <= 0) return;
-    // Splits (sample ranges) per group: one workgroup per compute unit (LDS; two
-    // with one plane) shared between the layers so that the longer of the two
-    // kinds of workgroup is as short as it can be.  A conv2 sample costs about
-    // COST2 / COST3 of a conv3 sample.  The counts are taken as padded for the
-    // XCDs: one workgroup too many on an XCD would run as a second round
-    // (batch 512: 58 us with 148 + 108 workgroups, 19 + 14 on an XCD's 32 units).
-    constexpr int COST2 = 9, COST3 = 5;  // 7500 and 4140 cycles
-    const int slots = max(1, cus) * (bf16 ? 2 : 1), most = min(n, WG_MAX_SPLITS / groups);
-    auto blocks_of = [&](int a, int b) {
-        return pad_xcd(Wg2::SLICES * a * groups) + pad_xcd(Wg3::SLICES * b * groups);
-    };
+// Splits (sample ranges) per group: one workgroup per slot, shared between the
+// layers so that the longer of the two kinds of workgroup is as short as it can
+// be; the length is returned.  A conv2 sample costs about COST2 / COST3 of a
+// conv3 sample.  The counts are taken as padded for the XCDs: one workgroup too
+// many on an XCD would run as a second round (batch 512: 58 us with 148 + 108
+// workgroups, 19 + 14 on an XCD's 32 units).
+constexpr int COST2 = 9, COST3 = 5;  // 7500 and 4140 cycles
+static int wgrad_splits(int slots, int groups, int n, int* s3, int* s2) {
+    const int most = min(n, WG_MAX_SPLITS / groups);
     int best = COST2 * n;  // one split of each, also where that is more than one round
     for (int a = 1; a <= most; ++a) {
         const int left = slots - pad_xcd(Wg2::SLICES * a * groups);
@@ -340,14 +355,62 @@ void launch_conv_wgrad(const float* dz3, bool dz3_bf16, const float* h2, const f
     const int per2 = max(1, best / COST2), per3 = max(1, best / COST3);
     *s2 = (n + per2 - 1) / per2;
     *s3 = (n + per3 - 1) / per3;
-    const int blocks = blocks_of(*s2, *s3);
-    auto go = [&](auto gp, auto* z3, auto* z2) {
-        conv_wgrad_kernel<decltype(gp)::value><<<blocks, WG_THREADS, 0, st>>>(
-            z3, h2, z2, h1, groups, n, *s3, *s2, part3, part2, bias3, bias2);
+    return best;
+}
+static int wgrad_blocks(int groups, int s3, int s2) {
+    return pad_xcd(Wg2::SLICES * s2 * groups) + pad_xcd(Wg3::SLICES * s3 * groups);
+}
+
+// Pairs of conv1 workgroups a group for one launch of all three layers, or 0
+// where conv1 keeps a launch of its own.  Beside the others conv1 costs them
+// units of the chip (a workgroup a unit, all resident at once), and saves its
+// own launch, 6.5 us at 32 rows, as long as a conv2 range is at most one sample
+// (3.3 us) longer.  A conv1 wave's unit of work costs about COST1.
+// Whole step, two launches -> one, us: 32 rows 97.3 -> 91.3.
+static int conv1_beside(int groups, int n, int cus, int* s3, int* s2) {
+    constexpr int COST1 = 5;
+    int pairs = 0, best = wgrad_splits(cus, groups, n, s3, s2) + COST2;
+    const int units = n * C1W_UNITS;
+    for (int k = 1; COST1 * k <= best; ++k) {  // units a wave
+        const int p = (units + C1W_WAVES * k - 1) / (C1W_WAVES * k), n1 = 2 * pad_xcd(p) * groups;
+        if (p > CONV1_WG_MAX_SPLITS / groups || n1 >= cus) continue;
+        int a3, a2;
+        const int len = max(COST1 * k, wgrad_splits(cus - n1, groups, n, &a3, &a2));
+        if (len > best || (pairs && len == best) || n1 + wgrad_blocks(groups, a3, a2) > cus) continue;
+        pairs = p;
+        best = len;
+        *s3 = a3;
+        *s2 = a2;
+    }
+    return pairs;
+}
+
+int launch_conv_wgrad(const float* dz3, bool dz3_bf16, const float* h2, const float* dz2, const float* h1,
+                      int groups, int n, float* part3, float* part2, float* bias3, float* bias2,
+                      int* s3, int* s2, const float* dz1, const uint8_t* const* ftab,
+                      const uint8_t* zero_frame, float* part1, float* bias1, bool bf16, int cus,
+                      hipStream_t st) {
+    *s3 = *s2 = 0;
+    if (n <= 0) return 0;
+    C1wPart c1;
+    if (!bf16) {
+        const int pairs = conv1_beside(groups, n, max(1, cus), s3, s2);
+        if (pairs) c1 = C1wPart{2 * pad_xcd(pairs), pairs, dz1, ftab, zero_frame, part1, bias1};
+    } else {  // one plane: two workgroups a unit
+        wgrad_splits(max(1, cus) * 2, groups, n, s3, s2);
+    }
+    const int blocks = c1.blocks * groups + wgrad_blocks(groups, *s3, *s2);
+    auto go = [&](auto gp, auto with1, auto* z3, auto* z2) {
+        conv_wgrad_kernel<decltype(gp)::value, decltype(with1)::value><<<blocks, WG_THREADS, 0, st>>>(
+            z3, h2, z2, h1, groups, n, *s3, *s2, part3, part2, bias3, bias2, c1);
     };
-    if (!bf16) go(std::integral_constant<int, 3>{}, dz3, dz2);
-    else if (!dz3_bf16) go(std::integral_constant<int, 1>{}, dz3, (const uint16_t*)dz2);
-    else go(std::integral_constant<int, 1>{}, (const uint16_t*)dz3, (const uint16_t*)dz2);
+    constexpr std::integral_constant<int, 3> fp32{};
+    constexpr std::integral_constant<int, 1> one{};
+    if (c1.blocks) go(fp32, std::true_type{}, dz3, dz2);
+    else if (!bf16) go(fp32, std::false_type{}, dz3, dz2);
+    else if (!dz3_bf16) go(one, std::false_type{}, dz3, (const uint16_t*)dz2);
+    else go(one, std::false_type{}, (const uint16_t*)dz3, (const uint16_t*)dz2);
+    return c1.splits;
 }
 
 }  // namespace gorila

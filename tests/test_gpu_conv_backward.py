@@ -38,7 +38,9 @@ def oracle_mod():
     return oracle
 
 
-@pytest.mark.parametrize("B", [1, 2, 64, 65, 128, 129, 257, 513])
+# also around the rows where conv1's weight gradient shares the others' launch:
+# one, two, three and four units of it a wave (32, 64, 96, 128), none (144)
+@pytest.mark.parametrize("B", [1, 2, 7, 32, 40, 64, 65, 96, 128, 129, 144, 257, 513])
 def test_fp32_rows(oracle_mod, B):
     import paper_1507_04296_amd as g
     print(f"[gpu-case] conv backward fp32 B={B}", flush=True)
@@ -68,5 +70,25 @@ def test_bf16_rows(oracle_mod, G, b):
            lambda: g.learner_step_grouped(ctx, th, tg, A, rep, _t(idx), inp.gamma, 1.0),
            [datagen.bf16_bits_to_f64(t) for t in inp.theta_bf16],
            datagen.bf16_bits_to_f64(inp.target_bf16), inp, idx, b, A, parity.GRAD_TOL_BF16)
+    ctx.check()
+    ctx.close()
+
+
+@pytest.mark.parametrize("G,b", [(2, 15), (2, 16), (2, 17), (4, 1)])
+def test_fp32_groups(oracle_mod, G, b):
+    """Several fp32 learners: conv1's weight gradient beside the others (and not)."""
+    import paper_1507_04296_amd as g
+    print(f"[gpu-case] conv backward fp32 G={G} b={b}", flush=True)
+    A = 5
+    inp = datagen.grouped_inputs(7500 + G * b, G, b, A)
+    ctx = g.Context(b, A, groups=G)
+    rep = g.Replay.stacked(_t(inp.s), _t(inp.s2), _t(inp.a), _t(inp.r), _t(inp.term))
+    th64 = [datagen.bf16_bits_to_f64(t) for t in inp.theta_bf16]
+    tg64 = datagen.bf16_bits_to_f64(inp.target_bf16)
+    th, tg = [_t(x.astype(np.float32)) for x in th64], _t(tg64.astype(np.float32))
+    idx = np.arange(G * b, dtype=np.int64)
+    _check(g, oracle_mod,
+           lambda: g.learner_step_grouped(ctx, th, tg, A, rep, _t(idx), inp.gamma, 1.0),
+           th64, tg64, inp, idx, b, A, parity.GRAD_TOL)
     ctx.check()
     ctx.close()
