@@ -366,7 +366,8 @@ static int wgrad_blocks(int groups, int s3, int s2) {
 // units of the chip (a workgroup a unit, all resident at once), and saves its
 // own launch, 6.5 us at 32 rows, as long as a conv2 range is at most one sample
 // (3.3 us) longer.  A conv1 wave's unit of work costs about COST1.
-// Whole step, two launches -> one, us: 32 rows 97.3 -> 91.3.
+// Whole step, two launches -> one, us: 8 rows 92.9 -> 86.6, 32 97.3 -> 91.3, 64 103.8
+// -> 99.0, 96 116.6 -> 110.1, 128 129.9 -> 120.7, 2 x 16 107.5 -> 101.2.
 static int conv1_beside(int groups, int n, int cus, int* s3, int* s2) {
     constexpr int COST1 = 5;
     int pairs = 0, best = wgrad_splits(cus, groups, n, s3, s2) + COST2;
