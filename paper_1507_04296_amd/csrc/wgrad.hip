@@ -73,13 +73,15 @@ __device__ __forceinline__ bf16x8 tr_read(const char* a, const char* b) {
 struct Wg2 {  // conv2, slice = 16 input channels; a wave: 4 row tiles x 2 taps
     static constexpr int SLICES = 2, PIX = P2, STEPS = 3, MT = 4, NT = 2, CG = 1;  // 81 pixels in 3 x 32
     static constexpr int XPIX = P1, XQ = 4;                                // h1 quads a pixel
-    static constexpr int A_ROW = 208, A_PLANE = 64 * A_ROW, X_PLANE = XPIX * 32;
+    static constexpr int A_ROW = 208, A_PLANE = 64 * A_ROW;
+    static constexpr int ZERO = XPIX * 32, X_PLANE = ZERO + 128;           // pixels 400 .. 403 are zeros
     static constexpr int LD = 16 * C1;                                     // columns of a partial
 };
 struct Wg3 {  // conv3, slice = one filter row; a wave: 2 row tiles x 3 taps of 16 channels
     static constexpr int SLICES = 3, PIX = P3, STEPS = 2, MT = 2, NT = 3, CG = 3;  // 49 pixels in 2 x 32
     static constexpr int XPIX = H3 * H2, XQ = 16;                          // 7 of the 9 rows of h2
-    static constexpr int A_ROW = 144, A_PLANE = 64 * A_ROW, X_PLANE = XPIX * 128;
+    static constexpr int A_ROW = 144, A_PLANE = 64 * A_ROW;
+    static constexpr int ZERO = 64 * 128, X_PLANE = ZERO + 6 * 128;        // pixels 64 .. 69 are zeros
     static constexpr int LD = 9 * C2;
 };
 template <int GP>
@@ -184,11 +186,12 @@ __device__ __forceinline__ void wgrad_run(char* lds, int slice, int b0, int b1, 
     int px[G::STEPS * 2];
 #pragma unroll
     for (int k = 0; k < G::STEPS * 2; ++k) {
-        const int s = 8 * (k >> 1) + 2 * q + (k & 1), mp = set_pixel<CONV2>(s, ri);
-        // padding multiplies zeros with a pixel that shares no bank with its set's
-        const int m = mp >= 0 ? mp : CONV2 ? P2 - 1 : s < 14 ? (s - 7) * H3 + 3 : 0;
+        const int s = 8 * (k >> 1) + 2 * q + (k & 1), m = set_pixel<CONV2>(s, ri);
         if (CONV2) px[k] = 2 * (m / H2) * H1 + 2 * (m % H2) + tu * H1 + tv;
         else px[k] = (m / H3) * H2 + m % H3;
+        // padding multiplies zeros with zeros (a real pixel's infinity would make
+        // NaNs of them); conv3's of a pixel that shares no bank with its set's
+        if (m < 0) px[k] = CONV2 ? P1 : 64 + (s & 3);
     }
 
     f32x4 hi[G::MT][G::NT], lo[G::MT][G::NT];
@@ -251,6 +254,14 @@ __device__ __forceinline__ void wgrad_run(char* lds, int slice, int b0, int b1, 
     };
     if (b0 < b1) {
         const int bn = min(b0 + 1, b1 - 1);
+        // the zero pixels of every plane of both buffers
+        constexpr int ZV = (G::X_PLANE - G::ZERO) / 16;
+        static_assert(2 * GP * ZV <= WG_THREADS, "one vector a thread");
+        if (tid < 2 * GP * ZV) {
+            const int pl = tid / ZV, half = pl / GP;  // plane pl % GP of buffer `half`
+            *(uint4*)(lds + half * BUF + GP * G::A_PLANE + (pl - half * GP) * G::X_PLANE + G::ZERO + (tid - pl * ZV) * 16) =
+                make_uint4(0, 0, 0, 0);
+        }
         fetch_a(b0);
 #pragma unroll
         for (int k = 0; k < TX; ++k) fetch_x(b0, k);
