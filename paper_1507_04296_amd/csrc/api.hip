@@ -730,7 +730,7 @@ int learner_steps(gorila_ctx* ctx, const gorila_params* params, int G, bool allo
     }
     {
         StageTimer t(ctx, ST_CONV_DGRAD);
-        launch_bwd_data(dz3, kp, h2, h1, fragd, G, b, dz2, dz1, bf16, ctx->cus, st);
+        launch_bwd_data(dz3, kp, h2, h1, fragd, on, G, b, dz2, dz1, bf16, ctx->cus, st);
     }
     {
         StageTimer t(ctx, ST_CONV_WGRAD);

@@ -5,7 +5,8 @@
 //   dz2[y][x][c] = [h2 > 0] sum_{u,v,o} W3[o][c][u][v] dz3[y-u][x-v][o]
 //   dz1[2y'+py][2x'+px][c] = [h1 > 0] sum_{du,dv,o} W2[o][c][2du+py][2dv+px] dz2[y'-du][x'-dv][o]
 // Both are stored with a border of zeros (11 x 11 pixels), so taps outside the
-// image need no test; pixel tiles for which a whole tap is outside skip it.
+// image need no test (but see inside_sum); pixel tiles for which a whole tap is
+// outside skip it.
 //
 // conv3: 6 tiles of 16 of the 81 pixels, 4 channel tiles, 9 taps x 64 o; a wave
 // takes three pixel tiles (mh), two channel tiles (nh) and 32 of the 64 o (kh),
@@ -24,6 +25,8 @@
 #include "common.h"
 #include "kernels.h"
 #include "planes.h"
+
+#include <type_traits>
 
 namespace gorila {
 
@@ -53,6 +56,11 @@ constexpr bool bd3_active(int t, int u, int v) {
 }
 // tiles of the two wave groups, chosen so that their active taps balance (19, 21)
 constexpr int BD3_TILE[2][3] = {{1, 2, 5}, {0, 3, 4}};
+__device__ inline int bd3_tile(int mh, int j) {  // the same for a j that is no constant
+    constexpr auto pack = [](int m) { return BD3_TILE[m][0] | BD3_TILE[m][1] << 4 | BD3_TILE[m][2] << 8; };
+    constexpr int T0 = pack(0), T1 = pack(1);
+    return (mh ? T1 : T0) >> (4 * j) & 15;
+}
 constexpr unsigned bd3_mask(int mh, int tap) {
     unsigned m = 0;
     for (int j = 0; j < 3; ++j) m |= bd3_active(BD3_TILE[mh][j], tap / 3, tap % 3) ? 1u << j : 0u;
@@ -126,13 +134,40 @@ __device__ __forceinline__ void tile_sequence(XLoad xload, bf16x8 (&w)[2][2][GP]
     });
 }
 
+// An infinite weight makes NaNs of the border's zeros (0 * inf), also in outputs
+// of which its tap is no part.  So a lane that has stored a NaN (`check`, the sum
+// of all it stored, is one too) forms such outputs again, one product at a time,
+// over the taps inside the image; a NaN that is one of those ends the sum.  (The
+// sums and the test: 90.5 -> 90.8 us of a step of 32 rows, 313.8 -> 314.8 of 512.)
+// z(tap u, v, o): the gradient's planes there, or null; w(u, v, o): the weight.
+template <int GP, int K, class Z, class W>
+__device__ __forceinline__ float inside_sum(Z z, W w) {
+    float t = 0.0f;
+#pragma unroll 1
+    for (int i = 0; i < K * K * 64 && t == t; ++i) {
+        const int u = i / (K * 64), v = i / 64 % K, o = i & 63;
+        const char* const p = z(u, v, o);
+        if (!p) continue;
+        float x = ldv((const uint16_t*)p);
+        if (fabsf(x) < INFINITY)  // (an infinite value's other planes are NaNs)
+#pragma unroll
+            for (int pl = 1; pl < GP; ++pl) x += ldv((const uint16_t*)(p + pl * BD_PLANE));
+        t = fmaf(w(u, v, o), x, t);
+    }
+    return t;
+}
+
+// Waves a SIMD: bf16 dz3 comes in steps of more than 128 rows, two workgroups a unit.
+template <class T>
+constexpr int BD_MIN_WAVES = std::is_same_v<T, float> ? 2 : 4;
+
 // GP planes of gradients and of weights: 3 for fp32 steps, 1 for bf16 ones
 // (gradients rounded to bf16).  dz3: `kp` partial planes [kp][rows][64][49] of
 // type T, added in order, the sum of more than one left as plane kp; dz2 [rows][81][64], dz1 [rows][400][32] of type O.
 template <int GP, class T, class O>
-__global__ __launch_bounds__(BD_THREADS) void bwd_data_kernel(
+__global__ __launch_bounds__(BD_THREADS, BD_MIN_WAVES<T>) void bwd_data_kernel(
     T* dz3, int kp, const float* __restrict__ h2, const float* __restrict__ h1,
-    GroupPtrs16 frags, int n, int rows, O* __restrict__ dz2, O* __restrict__ dz1) {
+    GroupPtrs16 frags, GroupPtrs theta, int n, int rows, O* __restrict__ dz2, O* __restrict__ dz1) {
     using L = BdLds<GP>;
     __shared__ __attribute__((aligned(16))) char lds[L::BYTES];
     char* const z3 = lds + L::Z3;
@@ -201,7 +236,9 @@ __global__ __launch_bounds__(BD_THREADS) void bwd_data_kernel(
 
     for (int r = blockIdx.x; r < rows; r += gridDim.x) {
         const int next = r + (int)gridDim.x;
-        frag = frags.p[r / n];
+        const int g = r / n;
+        frag = frags.p[g];
+        const float* const th = theta.p[g];
         // an offset of 0 that the compiler cannot see through: the weights are
         // read again for every sample, not kept over the row loop
         asm volatile("" : "+s"(zero));
@@ -277,6 +314,7 @@ __global__ __launch_bounds__(BD_THREADS) void bwd_data_kernel(
             __syncthreads();
             const int el = opaque(lane), c0 = (nh * 2 + kh) * 16 + 4 * (el >> 4);
             O* const out = dz2 + (int64_t)r * P2 * C2;
+            float check = 0.0f;
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
                 const f32x4 part = xch[((wave ^ 1) * 3 + j) * 64 + lane];
@@ -286,15 +324,36 @@ __global__ __launch_bounds__(BD_THREADS) void bwd_data_kernel(
                     f32x4 v;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] = m >> e & 1u ? hi[0][j][e] + part[e] : 0.0f;
+                    const int y = p / H2, x = p - y * H2;
+                    check += (v[0] + v[1]) + (v[2] + v[3]);
                     bf16x4 o[GP];
                     split4<GP>(v, o);
-                    const int y = p / H2, x = p - y * H2;
                     const int off = bd_off((y + 1) * BD_W + x + 1, (y + 1) * 10 + x + 1, c0 >> 3) + ((c0 & 4) << 1);
 #pragma unroll
                     for (int pl = 0; pl < GP; ++pl) *(bf16x4*)(z2 + pl * BD_PLANE + off) = o[pl];
                     stq(out + p * C2 + c0, v);
                 }
             }
+            if (__builtin_expect(check != check, 0))
+#pragma unroll 1
+                for (int k = 0; k < 12; ++k) {  // channel c0 + k % 4 of the wave's tile k / 4
+                    const int p = bd3_tile(mh3, k >> 2) * 16 + (el & 15), c = c0 + (k & 3);
+                    if (p >= P2 || ldv(out + p * C2 + c) == ldv(out + p * C2 + c)) continue;
+                    const int y = p / H2, x = p - y * H2;
+                    const float t = inside_sum<GP, K3>(
+                        [&](int u, int v, int o) -> const char* {
+                            const int i = y - u, j = x - v;
+                            if (i < 0 || i >= H3 || j < 0 || j >= H3) return nullptr;
+                            return z3 + bd_off((i + 2) * BD_W + j + 2, (i + 2) * H2 + j + 2, o >> 3) + (o & 7) * 2;
+                        },
+                        [&](int u, int v, int o) { return th[OFF_W3 + ((o * C2 + c) * K3 + u) * K3 + v]; });
+                    stv(out + p * C2 + c, t);
+                    bf16x4 o[GP];
+                    split4<GP>(f32x4{t, 0.f, 0.f, 0.f}, o);
+                    char* const to = z2 + bd_off((y + 1) * BD_W + x + 1, (y + 1) * 10 + x + 1, c >> 3) + (c & 7) * 2;
+#pragma unroll
+                    for (int pl = 0; pl < GP; ++pl) *(__bf16*)(to + pl * BD_PLANE) = o[pl][0];
+                }
         }
         __syncthreads();
 
@@ -333,6 +392,7 @@ __global__ __launch_bounds__(BD_THREADS) void bwd_data_kernel(
                 }
                 const int el = opaque(lane), c0 = 4 * (el >> 4);
                 O* const out = dz1 + (int64_t)r * P1 * C1;
+                float check = 0.0f;
 #pragma unroll
                 for (int j = 0; j < NT; ++j) {
                     const int m = (MH * 4 + j) * 16 + (el & 15), y = m / 10, x0 = m - y * 10;
@@ -344,10 +404,28 @@ __global__ __launch_bounds__(BD_THREADS) void bwd_data_kernel(
                             f32x4 v;
 #pragma unroll
                             for (int e = 0; e < 4; ++e) v[e] = b >> e & 1u ? plane_sum<GP>(hi[i][j][e], lo[i][j][e]) : 0.0f;
+                            check += (v[0] + v[1]) + (v[2] + v[3]);
                             stq(out + p * C1 + i * 16 + c0, v);
                         }
                     }
                 }
+                if (__builtin_expect(check != check, 0))
+#pragma unroll 1
+                    for (int k = 0; k < 8 * NT; ++k) {  // channel of tile k / 8
+                        const int m = (MH * 4 + (k >> 3)) * 16 + (el & 15), y = m / 10, x = m - y * 10;
+                        const int p = (2 * y + (ph >> 1)) * H1 + 2 * x + (ph & 1), c = (k >> 2 & 1) * 16 + c0 + (k & 3);
+                        if (m >= 100 || ldv(out + p * C1 + c) == ldv(out + p * C1 + c)) continue;
+                        stv(out + p * C1 + c,
+                            inside_sum<GP, 2>(
+                                [&](int du, int dv, int o) -> const char* {
+                                    const int i = y - du, j = x - dv;
+                                    if (i < 0 || i >= H2 || j < 0 || j >= H2) return nullptr;
+                                    return z2 + bd_off((i + 1) * BD_W + j + 1, (i + 1) * 10 + j + 1, o >> 3) + (o & 7) * 2;
+                                },
+                                [&](int du, int dv, int o) {
+                                    return th[OFF_W2 + ((o * C1 + c) * K2 + 2 * du + (ph >> 1)) * K2 + 2 * dv + (ph & 1)];
+                                }));
+                    }
             };
             if (mh2) run(std::integral_constant<int, 1>{});
             else run(std::integral_constant<int, 0>{});
@@ -357,21 +435,21 @@ __global__ __launch_bounds__(BD_THREADS) void bwd_data_kernel(
 }
 
 void launch_bwd_data(float* dz3, int kp, const float* h2, const float* h1,
-                     const GroupPtrs16& frags, int groups, int n, float* dz2, float* dz1, bool bf16,
-                     int cus, hipStream_t st) {
+                     const GroupPtrs16& frags, const GroupPtrs& theta, int groups, int n, float* dz2,
+                     float* dz1, bool bf16, int cus, hipStream_t st) {
     const int rows = groups * n;
     if (rows <= 0) return;
     // resident workgroups per compute unit (LDS): one with three planes, two with one
     const int blocks = min(rows, max(cus, 1) * (bf16 ? 2 : 1));
     if (!bf16)
-        bwd_data_kernel<3, float, float><<<blocks, BD_THREADS, 0, st>>>(dz3, kp, h2, h1, frags, n, rows,
+        bwd_data_kernel<3, float, float><<<blocks, BD_THREADS, 0, st>>>(dz3, kp, h2, h1, frags, theta, n, rows,
                                                                         dz2, dz1);
     else if (kp > 1)
         bwd_data_kernel<1, float, uint16_t><<<blocks, BD_THREADS, 0, st>>>(
-            dz3, kp, h2, h1, frags, n, rows, (uint16_t*)dz2, (uint16_t*)dz1);
+            dz3, kp, h2, h1, frags, theta, n, rows, (uint16_t*)dz2, (uint16_t*)dz1);
     else  // dz3 as the fc1 backward rounded it
         bwd_data_kernel<1, uint16_t, uint16_t><<<blocks, BD_THREADS, 0, st>>>(
-            (uint16_t*)dz3, kp, h2, h1, frags, n, rows, (uint16_t*)dz2, (uint16_t*)dz1);
+            (uint16_t*)dz3, kp, h2, h1, frags, theta, n, rows, (uint16_t*)dz2, (uint16_t*)dz1);
 }
 
 }  // namespace gorila

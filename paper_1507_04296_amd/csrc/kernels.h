@@ -262,10 +262,11 @@ int launch_fc1_backward(const float* dz4, const GroupPtrs& theta, const GroupPtr
 // dz2 [rows][81][64] and dz1 [rows][400][32] from kp planes of dz3 (bwd.hip),
 // whose fp32 sum is left as plane kp (kp > 1).
 // Outputs fp32, or (bf16) rounded to bf16, as the weight gradients read them;
-// frags.p[g]: learner group g's FRAGD fragments, three planes (bf16: one).
+// frags.p[g]: learner group g's FRAGD fragments, three planes (bf16: one);
+// theta.p[g]: its flat fp32 parameters.
 void launch_bwd_data(float* dz3, int kp, const float* h2, const float* h1,
-                     const GroupPtrs16& frags, int groups, int n, float* dz2, float* dz1, bool bf16,
-                     int cus, hipStream_t st);
+                     const GroupPtrs16& frags, const GroupPtrs& theta, int groups, int n, float* dz2,
+                     float* dz1, bool bf16, int cus, hipStream_t st);
 // Split partials of dW3 / db3 and dW2 / db2 in one launch (wgrad.hip; dz3 and
 // dz2 as above, dz3 one plane); *s3, *s2: splits per group.  Small fp32 steps'
 // launch takes conv1's partials (dz1 .. bias1 as launch_conv1_wgrad) too and
