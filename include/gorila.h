@@ -150,8 +150,13 @@ const char* gorila_strerror(int code);
  * gorila_ctx_timing_end synchronises the stream, writes for each of the first
  * n_stages stages the summed milliseconds (total_ms) and the number of
  * recorded launches (count), and stops recording.  Stage numbers and names:
- * gorila_stage_name(i) (NULL past the last stage).  Timing does not change
- * any result. */
+ * gorila_stage_name(i) (NULL past the last stage).  A stage that a call does not
+ * run as a launch of its own has no records: forward and act calls, and the
+ * target's rows of some learner steps, run conv1_fwd to conv3_fwd as conv_fwd;
+ * conv_dgrad and conv_wgrad hold the data and the weight gradients of conv3 and
+ * conv2 (small fp32 steps' conv_wgrad also conv1's, in place of conv1_wgrad);
+ * conv3_bwd and conv2_bwd are never recorded.  Timing does not change any
+ * result. */
 int gorila_ctx_timing_begin(gorila_ctx* ctx, uint32_t stage_mask, int32_t max_records);
 int gorila_ctx_timing_end(gorila_ctx* ctx, double* total_ms, int32_t* count, int32_t n_stages);
 const char* gorila_stage_name(int32_t stage);

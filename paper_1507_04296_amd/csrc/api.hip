@@ -13,17 +13,20 @@
 using namespace gorila;
 
 namespace {
-// Stages of the calls, in launch order (bits of the timing mask).  The
-// minibatch resolution (or a forward call's frame table) shares the prep
-// launch; conv_fwd is conv1 to conv3 in one launch, where a call runs them so.
+// Stages of the calls (bits of the timing mask).  The minibatch resolution (or a
+// forward call's frame table) shares the prep launch; conv_fwd is conv1 to conv3
+// in one launch, where a call runs them so.  Callers hold numbers and names, so
+// both stay: new stages go last, and conv3_bwd and conv2_bwd, whose launches
+// conv_dgrad and conv_wgrad took the place of, are kept and never recorded.
 enum Stage {
     ST_PREP, ST_CONV1_FWD, ST_CONV2_FWD, ST_CONV3_FWD, ST_FC1_FWD, ST_HEAD,
-    ST_FC1_BWD, ST_CONV_DGRAD, ST_CONV_WGRAD, ST_CONV1_WGRAD, ST_GRAD_REDUCE, ST_CONV_FWD, ST_COUNT
+    ST_FC1_BWD, ST_CONV3_BWD, ST_CONV2_BWD, ST_CONV1_WGRAD, ST_GRAD_REDUCE,
+    ST_CONV_FWD, ST_CONV_DGRAD, ST_CONV_WGRAD, ST_COUNT
 };
 const char* const STAGE_NAMES[ST_COUNT] = {
     "prep_weights", "conv1_fwd", "conv2_fwd", "conv3_fwd", "fc1_fwd", "head",
-    "fc1_bwd", "conv_dgrad", "conv_wgrad", "conv1_wgrad", "grad_reduce",
-    "conv_fwd"};
+    "fc1_bwd", "conv3_bwd", "conv2_bwd", "conv1_wgrad", "grad_reduce",
+    "conv_fwd", "conv_dgrad", "conv_wgrad"};
 struct TimingRecord {
     int stage;
     hipEvent_t start, stop;

@@ -106,3 +106,12 @@ def test_workspace_rejects_too_many_groups():
     import paper_1507_04296_amd as g
     assert g.workspace_bytes(64, 18, g.GORILA_BF16, 16) > 0
     assert g.workspace_bytes(64, 18, g.GORILA_BF16, 17) == 0
+
+
+def test_stage_numbers_and_names_stay():
+    """Callers hold timing masks and names: a stage keeps its number, new ones follow."""
+    import paper_1507_04296_amd as g
+    assert g.stage_names()[:11] == [
+        "prep_weights", "conv1_fwd", "conv2_fwd", "conv3_fwd", "fc1_fwd", "head", "fc1_bwd",
+        "conv3_bwd", "conv2_bwd", "conv1_wgrad", "grad_reduce"]
+    assert len(set(g.stage_names())) == len(g.stage_names()) <= 32
