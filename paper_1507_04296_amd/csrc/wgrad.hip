@@ -376,12 +376,21 @@ static int wgrad_blocks(int groups, int s3, int s2) {
 // where conv1 keeps a launch of its own.  Beside the others conv1 costs them
 // units of the chip (a workgroup a unit, all resident at once), and saves its
 // own launch, 6.5 us at 32 rows, as long as a conv2 range is at most one sample
-// (3.3 us) longer.  A conv1 wave's unit of work costs about COST1.
-// Whole step, two launches -> one, us: 8 rows 92.9 -> 86.6, 32 97.3 -> 91.3, 64 103.8
-// -> 99.0, 96 116.6 -> 110.1, 128 129.9 -> 120.7, 2 x 16 107.5 -> 101.2.
+// (3.3 us) longer.  A conv1 wave's unit of work costs about COST1.  Ranges are
+// whole samples, so beyond the smallest sizes that holds where the two-launch
+// ranges had slack: on 256 units for one learner of 1 .. 132, 145 .. 153, 161 ..
+// 182 and 229 .. 234 rows, for two of up to 64, 73 .. 76, 81 .. 89 and 115, for
+// four of up to 32, 37, 38, 41 .. 44 and 57; never with more rows than units.
+// Whole step, two launches -> one, us: 8 rows 92.9 -> 86.6, 32 97.3 -> 91.3, 64
+// 103.8 -> 99.0, 96 116.6 -> 110.3, 128 128.6 -> 120.1, 150 146.2 -> 137.5, 176
+// 153.7 -> 146.7, 230 185.0 -> 175.4, 2 x 16 107.5 -> 101.2, 2 x 85 158.4 -> 150.5,
+// 4 x 42 164.1 -> 156.3, 5 x 44 203.1 -> 187.7, 8 x 6 154.4 -> 150.0.
+// (bf16 steps keep two launches: with one plane the others take 52 KB of LDS, two
+// workgroups a unit, and conv1's 133 KB in the same launch would leave one.)
 static int conv1_beside(int groups, int n, int cus, int* s3, int* s2) {
     constexpr int COST1 = 5;
     int pairs = 0, best = wgrad_splits(cus, groups, n, s3, s2) + COST2;
+    if (groups * n > cus) return 0;  // (the search would say so, after up to 100 us)
     const int units = n * C1W_UNITS;
     for (int k = 1; COST1 * k <= best; ++k) {  // units a wave
         const int p = (units + C1W_WAVES * k - 1) / (C1W_WAVES * k), n1 = 2 * pad_xcd(p) * groups;

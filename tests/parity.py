@@ -74,6 +74,14 @@ def assert_td_close(q, q_next, td, ref, clip, q_tol=Q_TOL):
     return errs
 
 
+def stages_of(ctx, call):
+    """(what `call` returns, names of the stages that it ran as launches of their own)."""
+    import paper_1507_04296_amd as g
+    ctx.timing_begin(g.stage_names(), 64)
+    out = call()
+    return out, set(ctx.timing_end())
+
+
 def tie_gap(q_oracle):
     """Top-2 gap of each row of Q, relative to max |Q| of the whole call."""
     q = np.asarray(q_oracle, np.float64)

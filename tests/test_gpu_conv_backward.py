@@ -18,8 +18,11 @@ def _t(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
-def _check(g, oracle_mod, call, thetas64, target64, inp, idx, b, A, tol):
-    grads, loss = call()
+def _check(g, oracle_mod, ctx, call, thetas64, target64, inp, idx, b, A, tol, shared):
+    (grads, loss), stages = parity.stages_of(ctx, call)
+    assert {"conv_dgrad", "conv_wgrad"} <= stages
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert ("conv1_wgrad" not in stages) == shared
     g2, l2 = call()
     assert torch.equal(grads, g2) and torch.equal(loss, l2)
     got, got_l = grads.cpu().numpy().reshape(len(thetas64), -1), loss.cpu().numpy()
@@ -39,9 +42,13 @@ def oracle_mod():
 
 
 # also around the rows where conv1's weight gradient shares the others' launch:
-# one, two, three and four units of it a wave (32, 64, 96, 128), none (144)
-@pytest.mark.parametrize("B", [1, 2, 7, 32, 40, 64, 65, 96, 128, 129, 144, 257, 513])
-def test_fp32_rows(oracle_mod, B):
+# one, two, three and four units of it a wave (32, 64, 96, 128), none (144), and
+# the sizes beyond where the others' ranges have room for it again
+@pytest.mark.parametrize("B,shared", [(1, True), (2, True), (7, True), (32, True), (40, True),
+                                      (64, True), (65, True), (96, True), (128, True), (129, True),
+                                      (144, False), (150, True), (176, True), (200, False),
+                                      (230, True), (257, False), (513, False)])
+def test_fp32_rows(oracle_mod, B, shared):
     import paper_1507_04296_amd as g
     print(f"[gpu-case] conv backward fp32 B={B}", flush=True)
     A = 5
@@ -49,9 +56,9 @@ def test_fp32_rows(oracle_mod, B):
     ctx = g.Context(B, A)
     rep = g.Replay.stacked(_t(inp.s), _t(inp.s2), _t(inp.a), _t(inp.r), _t(inp.term))
     th, tg, idx = _t(inp.theta), _t(inp.theta_target), _t(inp.idx)
-    _check(g, oracle_mod, lambda: g.learner_step(ctx, th, tg, A, rep, idx, inp.gamma, 1.0),
+    _check(g, oracle_mod, ctx, lambda: g.learner_step(ctx, th, tg, A, rep, idx, inp.gamma, 1.0),
            [inp.theta.astype(np.float64)], inp.theta_target.astype(np.float64), inp, inp.idx, B, A,
-           parity.GRAD_TOL)
+           parity.GRAD_TOL, shared)
     ctx.check()
     ctx.close()
 
@@ -66,16 +73,17 @@ def test_bf16_rows(oracle_mod, G, b):
     rep = g.Replay.stacked(_t(inp.s), _t(inp.s2), _t(inp.a), _t(inp.r), _t(inp.term))
     th, tg = _t(inp.theta_bf16.view(np.int16)), _t(inp.target_bf16.view(np.int16))
     idx = np.arange(G * b, dtype=np.int64)
-    _check(g, oracle_mod,
+    _check(g, oracle_mod, ctx,
            lambda: g.learner_step_grouped(ctx, th, tg, A, rep, _t(idx), inp.gamma, 1.0),
            [datagen.bf16_bits_to_f64(t) for t in inp.theta_bf16],
-           datagen.bf16_bits_to_f64(inp.target_bf16), inp, idx, b, A, parity.GRAD_TOL_BF16)
+           datagen.bf16_bits_to_f64(inp.target_bf16), inp, idx, b, A, parity.GRAD_TOL_BF16, False)
     ctx.check()
     ctx.close()
 
 
-@pytest.mark.parametrize("G,b", [(2, 15), (2, 16), (2, 17), (4, 1)])
-def test_fp32_groups(oracle_mod, G, b):
+@pytest.mark.parametrize("G,b,shared", [(2, 15, True), (2, 16, True), (2, 17, True), (4, 1, True),
+                                        (2, 85, True), (4, 42, True), (2, 70, False), (4, 33, False)])
+def test_fp32_groups(oracle_mod, G, b, shared):
     """Several fp32 learners: conv1's weight gradient beside the others (and not)."""
     import paper_1507_04296_amd as g
     print(f"[gpu-case] conv backward fp32 G={G} b={b}", flush=True)
@@ -87,9 +95,9 @@ def test_fp32_groups(oracle_mod, G, b):
     tg64 = datagen.bf16_bits_to_f64(inp.target_bf16)
     th, tg = [_t(x.astype(np.float32)) for x in th64], _t(tg64.astype(np.float32))
     idx = np.arange(G * b, dtype=np.int64)
-    _check(g, oracle_mod,
+    _check(g, oracle_mod, ctx,
            lambda: g.learner_step_grouped(ctx, th, tg, A, rep, _t(idx), inp.gamma, 1.0),
-           th64, tg64, inp, idx, b, A, parity.GRAD_TOL)
+           th64, tg64, inp, idx, b, A, parity.GRAD_TOL, shared)
     ctx.check()
     ctx.close()
 
