@@ -71,3 +71,51 @@ def test_gradient_rows(G, b, bf16):
                                   inp.r[rows], inp.term[rows], inp.gamma, 1.0)
         parity.assert_grads_close(got[i], ref["grads"], A, tol)
         assert abs(got_l[i] - ref["loss"]) <= parity.LOSS_TOL * abs(ref["loss"])
+
+
+def _kernels(call):
+    """Names of the kernels that `call` launches."""
+    from torch.profiler import ProfilerActivity, profile
+    call()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    names = " ".join(e.name for e in p.events())
+    if "gorila" not in names:
+        pytest.skip("the profiler names no kernels here")
+    return names
+
+
+@pytest.mark.parametrize("n,planes", [(192, False), (193, True)])
+def test_forward_tiles(n, planes):
+    """The rows above are on the side of the line that they are meant for."""
+    import paper_1507_04296_amd as g
+    print(f"[gpu-case] fc1 forward tiles n={n}", flush=True)
+    A = 18
+    inp = datagen.actor_inputs(7500 + n, n, A)
+    ctx = g.Context((n + 1) // 2, A)
+    theta, states = _t(inp.theta), _t(inp.states)
+    names = _kernels(lambda: g.q_forward(ctx, theta, A, states))
+    assert ("PgFwdJob" in names) == planes and ("Fc1FwdJob" in names) != planes
+    ctx.close()
+
+
+@pytest.mark.parametrize("G,b,bf16,planes", [(1, 320, False, False), (1, 321, False, True),
+                                             (2, 64, True, False), (9, 15, True, True)])
+def test_gradient_tiles(G, b, bf16, planes):
+    import paper_1507_04296_amd as g
+    print(f"[gpu-case] fc1 backward tiles G={G} b={b} bf16={bf16}", flush=True)
+    A = 5
+    inp = datagen.grouped_inputs(7600 + G * b, G, b, A)
+    rep = g.Replay.stacked(_t(inp.s), _t(inp.s2), _t(inp.a), _t(inp.r), _t(inp.term))
+    idx = _t(np.arange(G * b, dtype=np.int64))
+    th, tg = _t(inp.theta_bf16.view(np.int16)), _t(inp.target_bf16.view(np.int16))
+    if not bf16:
+        th = [_t(datagen.bf16_bits_to_f64(x).astype(np.float32)) for x in inp.theta_bf16]
+        tg = _t(datagen.bf16_bits_to_f64(inp.target_bf16).astype(np.float32))
+    ctx = g.Context(b, A, groups=G, dtype=g.GORILA_BF16 if bf16 else g.GORILA_F32)
+    names = _kernels(lambda: g.learner_step_grouped(ctx, th, tg, A, rep, idx, inp.gamma, 1.0))
+    assert ("PgWgradJob" in names) == planes and ("Fc1WgradJob" in names) != planes
+    ctx.check()
+    ctx.close()

@@ -36,7 +36,8 @@ def test_q_of_every_round(n, bf16):
     states[0, :2] = 0          # blank channels, as at an episode start
     states[-1] = 255           # the largest input
     ctx = g.Context((n + 1) // 2, A, dtype=g.dtype_of(t))
-    q = g.q_forward(ctx, t, A, torch.from_numpy(states).to(dev))
+    q, stages = parity.stages_of(ctx, lambda: g.q_forward(ctx, t, A, torch.from_numpy(states).to(dev)))
+    assert "conv_fwd" in stages and "conv1_fwd" not in stages
     ctx.check()
     rows = sorted({r for r in (0, 1, 254, 255, 256, 300, 511, 512, n - 1) if r < n})
     ref = oracle.q_forward(oracle.Net(n_actions=A), theta, states[rows])
@@ -52,10 +53,11 @@ def test_q_of_every_round(n, bf16):
 
 
 # the rows where the choice changes with 256 units, and bf16's first round
-@pytest.mark.parametrize("G,b,bf16", [(1, 230, False), (1, 231, False), (7, 33, False),
-                                      (1, 460, False), (1, 461, False), (1, 615, False),
-                                      (2, 128, True), (4, 115, True), (4, 116, True)])
-def test_target_rows(G, b, bf16):
+@pytest.mark.parametrize("G,b,bf16,one", [
+    (1, 230, False, False), (1, 231, False, True), (7, 33, False, True), (1, 460, False, False),
+    (1, 461, False, True), (1, 614, False, False), (1, 615, False, True), (2, 128, True, False),
+    (4, 115, True, False), (4, 116, True, True)])
+def test_target_rows(G, b, bf16, one):
     """Against the fp64 oracle, at the bars of every learner test."""
     print(f"[gpu-case] target rows G={G} b={b} bf16={bf16}", flush=True)
     A = 18
@@ -71,7 +73,10 @@ def test_target_rows(G, b, bf16):
         th, tg = t(inp.theta_bf16.view(np.int16)), t(inp.target_bf16.view(np.int16))
     else:
         th, tg = [t(x.astype(np.float32)) for x in th64], t(tg64.astype(np.float32))
-    grads, loss = g.learner_step_grouped(ctx, th, tg, A, rep, t(idx), inp.gamma, 1.0)
+    (grads, loss), stages = parity.stages_of(
+        ctx, lambda: g.learner_step_grouped(ctx, th, tg, A, rep, t(idx), inp.gamma, 1.0))
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert ("conv_fwd" in stages) == one
     ctx.check()
     ctx.close()
     got, got_l = grads.cpu().numpy().reshape(G, -1), loss.cpu().numpy()
