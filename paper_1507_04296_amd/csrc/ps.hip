@@ -147,21 +147,24 @@ __global__ __launch_bounds__(256) void ps_plan_kernel(const uint8_t* __restrict_
 // consecutive elements; the values of up to PS_CHUNK applied gradients are
 // loaded before any is used, so many independent loads are in flight.
 //
-// With the library's square root and division the vector units bound it (16
-// gradients of 1693362 elements, 135.5 MB: 31.0 us).  Where nothing under- or
-// overflows (`fast`: lr and eps allow it) both are one reciprocal approximation
-// and one exact-residual correction (Markstein 1990): the library's rounding or
-// the neighbouring value; elsewhere the library's forms run.  23.1 us, 5.9 TB/s:
-// HBM.  (16-byte loads at the rows' 8-byte alignment: 36.8 us.)
+// With the library's square root and division the vector units bound it.  Where
+// nothing under- or overflows (`fast`: lr and eps allow it) both are shorter, with
+// the same bits: the root is its reciprocal's approximation and one correction by
+// the exact residual, the quotient the rounded reciprocal (the approximation and
+// one Newton step) and such a correction, which rounds as the division does
+// (Markstein 1990).  That every root of [1, 4) and every reciprocal of [1, 2) of
+// this approximation comes out rounded was checked value by value on the device
+// (powers of four and of two scale them exactly).  Elsewhere the library's forms
+// run.  (16-byte loads at the rows' 8-byte alignment: 36.8 us in place of 23.1.)
 __device__ __forceinline__ void adagrad(float& th, float& h, float g, float lr, float eps, bool fast) {
     h = h + g * g;
     const float a = lr * g;
-    if (fast && h > 0x1p-80f && h < 0x1p80f) {
+    if (fast && h > 0x1p-80f && h < 0x1p80f && !(fabsf(a) < 0x1p-80f && a != 0.0f)) {
         const float y = __builtin_amdgcn_rsqf(h), s0 = h * y;
         const float s = fmaf(0.5f * fmaf(-s0, s0, h), y, s0);  // sqrt(h)
-        const float d = eps + s;
-        const float r = __builtin_amdgcn_rcpf(d), q0 = a * r;
-        th -= fmaf(fmaf(-q0, d, a), r, q0);  // a / d
+        const float d = eps + s, r0 = __builtin_amdgcn_rcpf(d), r = fmaf(fmaf(-d, r0, 1.0f), r0, r0);
+        const float q = a * r;
+        th -= fmaf(fmaf(-q, d, a), r, q);  // a / d
     } else {
         th -= a / (eps + sqrtf(h));
     }
@@ -174,7 +177,7 @@ __global__ __launch_bounds__(256) void ps_apply_kernel(float* __restrict__ theta
                                                        float lr, float eps) {
     constexpr int ILP = PS_ELEMS / VEC;
     using IO = VecIO<VEC>;
-    const bool fast = lr < 0x1p60f && eps < 0x1p60f;
+    const bool fast = lr < 0x1p60f && eps < 0x1p40f;
     // n < 2^31 (checked by the caller): every vector index fits 32 bits
     const uint32_t nv = (uint32_t)(n / VEC);  // vectors (n is a multiple of VEC)
     const uint32_t stride = gridDim.x * 256u * ILP;
