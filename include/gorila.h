@@ -28,6 +28,9 @@
  *    W1 [32,4,8,8], b1 [32], W2 [64,32,4,4], b2 [64], W3 [64,64,3,3], b3 [64],
  *    W4 [512,3136], b4 [512], W5 [A,512], b5 [A]; the FC input is conv3's
  *    output flattened channel-major.  gorila_param_count(A) elements.
+ *  - fp32 products are formed to fp32 precision, many of them from exact bf16
+ *    terms of each operand: an operand of 0x1.ffp127 (3.396e38) and more counts
+ *    as infinite there, and one below about 2^-110 loses low bits.
  *  - Not thread-safe per context: calls on one context must not overlap.
  */
 #ifndef GORILA_H

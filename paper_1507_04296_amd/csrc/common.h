@@ -24,6 +24,10 @@ namespace gorila {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+// the same, and four bf16 bit patterns, at any element's address
+typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t u16x4a __attribute__((ext_vector_type(4), aligned(2)));
 
 constexpr int IN_C = 4, IN_H = 84, IN_W = 84;
 constexpr int FRAME_BYTES = IN_H * IN_W;          // 7056 = 441 x 16 bytes
@@ -149,6 +153,7 @@ struct IsMaskEpi<T, std::void_t<decltype(T::MASK)>> : std::bool_constant<T::MASK
 // ---------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 template <int ROWS, int PL>
 struct Bf16Tile {
@@ -163,8 +168,6 @@ struct Bf16Tile {
     __device__ static inline void put(char* s, int row, int k, f32x4 v) {
         // two values per rounding instruction; a rounded pair widens back by
         // moving each half to the top of a word, and the residual is exact
-        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-        typedef float f32x2 __attribute__((ext_vector_type(2)));
         const bf16x2 h01 = __builtin_convertvector(f32x2{v[0], v[1]}, bf16x2);
         const bf16x2 h23 = __builtin_convertvector(f32x2{v[2], v[3]}, bf16x2);
         const bf16x4 hi = __builtin_shufflevector(h01, h23, 0, 1, 2, 3);
@@ -635,38 +638,35 @@ struct TailSplit {
         return true;
     }
 };
-// The split for a job of job_tiles tiles of `chunks` chunks that closes a
-// launch of launch_tiles equal tiles on `cus` compute units, in pieces of at
-// least two chunks:
-//  - a small launch (at most half a tile per unit): every tile of the job in
-//    two pieces.  A workgroup costs ~5 us before its first chunk and after
+// The split for a launch of `tiles` equal tiles of `chunks` chunks on `cus`
+// compute units, in pieces of at least two chunks:
+//  - a small launch (at most half a tile per unit): every tile in two pieces.  A workgroup costs ~5 us before its first chunk and after
 //    its last (per-workgroup timestamps at batch 32), and each further piece
 //    adds a round trip to the hand-off, so more pieces measured slower;
-//  - otherwise the r = launch_tiles mod cus excess tiles, taken from this
-//    job, in up to 16 pieces, about one per unit -- only when the whole tiles
+//  - otherwise the last r = tiles mod cus, which are in excess of whole rounds,
+//    in up to 16 pieces, about one per unit -- only when the whole tiles
 //    fit in one round of `slots` workgroups per unit (the residency of the
 //    kernel: four for the double-buffered GEMMs here), so that the pieces
 //    start alongside them: behind a full round they would only start as whole
 //    tiles finish (measured no faster).
-inline TailSplit plan_split(float* ws, int* cnt, int cus, int launch_tiles, int job_tiles,
-                            int chunks, int slots = 4) {
+inline TailSplit plan_split(float* ws, int* cnt, int cus, int tiles, int chunks, int slots = 4) {
     TailSplit ts;
     ts.ws = ws;
     ts.cnt = cnt;
-    if (!ws || !cnt || cus < 1 || launch_tiles < 1) return ts;
+    if (!ws || !cnt || cus < 1 || tiles < 1) return ts;
     int r, p = SPLIT_MAX_PIECES;
     if (chunks / 2 < p) p = chunks / 2;
-    if (2 * launch_tiles <= cus) {
-        r = job_tiles;
+    if (2 * tiles <= cus) {
+        r = tiles;
         if (p > 2) p = 2;
     } else {
-        if (launch_tiles < cus) return ts;
-        r = launch_tiles % cus;
-        if (r == 0 || r > job_tiles || launch_tiles - r > slots * cus) return ts;
+        if (tiles < cus) return ts;
+        r = tiles % cus;
+        if (r == 0 || tiles - r > slots * cus) return ts;
         if (cus / r < p) p = cus / r;
     }
     if (p < 2 || r > SPLIT_MAX_TILES || r * p > SPLIT_MAX_SLOTS) return ts;
-    ts.full = job_tiles - r;
+    ts.full = tiles - r;
     ts.tail = r;
     ts.pieces = p;
     return ts;

@@ -1,8 +1,8 @@
-// Convolution 2/3 and FC-512 layers, forward, weight gradients and (FC-512)
-// data gradient, as implicit GEMMs
-// on the fp32 MFMA tile engine (common.h).  Shapes follow Section 5.1 of the
-// paper; the backward pass is the exact gradient of those layers (eq. (2)
-// needs grad_theta Q(s, a; theta)).
+// Convolution 2/3 forward, FC-512 forward and both its gradients as implicit
+// GEMMs on the fp32 MFMA tile engine (common.h), the choice between those and
+// the FC layer's plane tiles (fc1_planes.h), and the final gradient reduction.
+// Shapes follow Section 5.1 of the paper; the backward pass is the exact
+// gradient of those layers (eq. (2) needs grad_theta Q(s, a; theta)).
 //
 // Every layer below is written as C[row][col] = sum_k A[row][k] * B[col][k]
 // plus an epilogue.  Reduction indices of convolutions are ordered
@@ -15,12 +15,6 @@
 #include <type_traits>
 
 namespace gorila {
-
-// dz3 leaves the fc1 backward as fp32, or in bf16 steps whose reduction is not
-// cut into parts (kp = 1) as bf16, rounded once to the precision its readers'
-// products take it in (half the bytes written and read).
-__device__ inline void stg(float* p, float v) { *p = v; }
-__device__ inline void stg(uint16_t* p, float v) { *p = __builtin_bit_cast(uint16_t, (__bf16)v); }
 
 // ---------------------------------------------------------------------------
 // conv2 forward: h2[m][o] = relu(b2[o] + sum_{u,v,c} W2[o][c][u][v] h1[b][2i+u][2j+v][c])
@@ -113,7 +107,7 @@ void launch_conv2_fwd(const float* h1, const GroupPtrs& w2t, const GroupPtrs& th
         return;
     }
     const int T = (n * P2 + 63) / 64 * groups;
-    const TailSplit ts = plan_split(sw.ws, sw.cnt, sw.cus, T, T, Conv2FwdJob<0>::CHUNKS, 6);
+    const TailSplit ts = plan_split(sw.ws, sw.cnt, sw.cus, T, Conv2FwdJob<0>::CHUNKS, 6);
     if (ts.tail) launch_jobs(st, Conv2FwdJob<0, true>{h1, w2t, theta, h2, n, groups, ts});
     else launch_jobs(st, Conv2FwdJob<0>{h1, w2t, theta, h2, n, groups, ts});
 }
@@ -191,7 +185,7 @@ void launch_conv3_fwd(const float* h2, const GroupPtrs& w3t, const GroupPtrs& th
                       int n, float* h3, const SplitWs& sw, bool bf16, hipStream_t st) {
     if (n <= 0) return;
     const int T = (n * P3 + 63) / 64 * groups;
-    const TailSplit ts = plan_split(sw.ws, sw.cnt, sw.cus, T, T, Conv3FwdJob<0>::CHUNKS);
+    const TailSplit ts = plan_split(sw.ws, sw.cnt, sw.cus, T, Conv3FwdJob<0>::CHUNKS);
     if (bf16 && ts.tail) launch_jobs(st, Conv3FwdJob<1, true>{h2, w3t, theta, h3, n, groups, ts});
     else if (bf16) launch_jobs(st, Conv3FwdJob<1>{h2, w3t, theta, h3, n, groups, ts});
     else if (ts.tail) launch_jobs(st, Conv3FwdJob<0, true>{h2, w3t, theta, h3, n, groups, ts});
@@ -380,7 +374,7 @@ struct Dz3Store {
     __device__ void operator()(int row, int col, float v, float m) const {
         const int b = r0 + row;
         if (b >= rows) return;
-        stg(dz3 + (int64_t)b * FLAT + c0 + col, m > 0.0f ? v : 0.0f);
+        dz3[(int64_t)b * FLAT + c0 + col] = m > 0.0f ? v : 0.0f;
     }
 };
 
@@ -555,10 +549,14 @@ int launch_fc1_backward(const float* dz4, const GroupPtrs& theta, const GroupPtr
         return row_blocks;
     }
     if (!bf16 && kp == 1 && n > 320) {
-        // Three planes: 128-row tiles, one workgroup a unit, pay once the batch
-        // fills them (rows 256: 25.4 against 22.5 us, 320: 26.3 against 25.9,
+        // Three planes: 128-row tiles, one workgroup a unit, pay once a learner's
+        // rows fill them (rows 256: 25.4 against 22.5 us, 320: 26.3 against 25.9,
         // 352: 26.4 against 29.4, 512: 30.4 against 34.2, 1024: 60 against 72;
-        // four learners of 33 rows: 28.8 against 22.3).
+        // four learners of 33 rows: 28.8 against 22.3).  Learners of up to 320
+        // rows are within 4 % either way, a whole step in these tiles against the
+        // fp32 ones: 8 x 128 557 against 569, 3 x 200 393 against 402, 4 x 128 305
+        // against 308, 2 x 256 309 against 309, 6 x 150 558 against 550, 2 x 192 262
+        // against 255, 16 x 64 609 against 601, 4 x 64 197 against 191.
         launch_jobs(st, PgWgradJob<128, 128, 3>{dz4, h3, grads, grads_stride, n, groups},
                     PgDgradJob<128, 128, 3, float>{dz4, theta, w4b, h3, dz3, n, groups}, hp);
         return row_blocks;

@@ -3,7 +3,10 @@
 // of the previous, 8 + 8 + 8 significant bits; bf16 values are one plane), and
 // of the nine plane products of two fp32 operands the three below 2^-24 of the
 // value (mid*lo, lo*mid, lo*lo) are left out.  Each plane product is exact in
-// fp32, so only the accumulation rounds.
+// fp32, so only the accumulation rounds.  An operand loses low bits below about
+// 2^-110, and one that rounds to bf16's infinity (finite, from 0x1.ffp127 =
+// 3.396e38 on) is infinite; infinite and NaN operands give the infinities and
+// NaNs of the fp32 instruction (plane_sum).
 //
 // Operand layout: lane l holds row (A) or column (B) l % 16 and the reduction
 // indices 8 (l / 16) .. +7; accumulator element e of lane l is row 4 (l / 16)
@@ -12,9 +15,6 @@
 #include "common.h"
 
 namespace gorila {
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // Four values as NP bf16 planes (two values per rounding; the remainders are exact).
 template <int NP>
@@ -108,8 +108,6 @@ __device__ inline float ldv(const uint16_t* p) { return __uint_as_float((uint32_
 __device__ inline void stv(float* p, float v) { *p = v; }
 __device__ inline void stv(uint16_t* p, float v) { *p = __builtin_bit_cast(uint16_t, (__bf16)v); }
 // The same quads at any element's address.
-typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint16_t u16x4a __attribute__((ext_vector_type(4), aligned(2)));
 __device__ inline f32x4 ldqa(const float* p) { return *(const f32x4a*)p; }
 __device__ inline f32x4 ldqa(const uint16_t* p) {
     const u16x4a v = *(const u16x4a*)p;

@@ -96,8 +96,6 @@ constexpr int PS_CHUNK = 4;   // gradients whose values are loaded together
 constexpr int PS_MAX_GROUPS = 4096;  // GORILA_PS_MAX_GROUPS
 constexpr int PS_MASK_WORDS = PS_MAX_GROUPS / 32;
 
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
 // Load / store VEC consecutive floats at vector index i (a 32-bit index, so
 // a uniform row base plus a per-lane offset addresses every access).
 template <int VEC> struct VecIO;
@@ -277,8 +275,6 @@ __device__ inline uint16_t f32_to_bf16_rne(float x) {
 // elements: only 2-byte (bf16) or 4-byte aligned); the last n % 4 elements one
 // by one.  Bound by HBM: the pull of 1693362 elements into 16 bf16 copies, 61
 // MB, took 12.2 us with 2-byte stores, and a second launch 3.9 us; now 11.1 us.
-typedef uint16_t u16x4a __attribute__((ext_vector_type(4), aligned(2)));
-typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));
 template <bool BF16>
 __global__ __launch_bounds__(256) void sync_copy_kernel(const float* __restrict__ src,
                                                         void* __restrict__ dst, int64_t n,
