@@ -146,26 +146,38 @@ __global__ __launch_bounds__(256) void ps_plan_kernel(const uint8_t* __restrict_
 // loaded before any is used, so many independent loads are in flight.
 //
 // With the library's square root and division the vector units bound it.  Where
-// nothing under- or overflows (`fast`: lr and eps allow it) both are shorter, with
-// the same bits: the root is its reciprocal's approximation and one correction by
-// the exact residual, the quotient the rounded reciprocal (the approximation and
-// one Newton step) and such a correction, which rounds as the division does
-// (Markstein 1990).  That every root of [1, 4) and every reciprocal of [1, 2) of
-// this approximation comes out rounded was checked value by value on the device
-// (powers of four and of two scale them exactly).  Elsewhere the library's forms
-// run.  (16-byte loads at the rows' 8-byte alignment: 36.8 us in place of 23.1.)
-__device__ __forceinline__ void adagrad(float& th, float& h, float g, float lr, float eps, bool fast) {
-    h = h + g * g;
-    const float a = lr * g;
-    if (fast && h > 0x1p-80f && h < 0x1p80f && !(fabsf(a) < 0x1p-80f && a != 0.0f)) {
-        const float y = __builtin_amdgcn_rsqf(h), s0 = h * y;
-        const float s = fmaf(0.5f * fmaf(-s0, s0, h), y, s0);  // sqrt(h)
-        const float d = eps + s, r0 = __builtin_amdgcn_rcpf(d), r = fmaf(fmaf(-d, r0, 1.0f), r0, r0);
-        const float q = a * r;
-        th -= fmaf(fmaf(-q, d, a), r, q);  // a / d
-    } else {
-        th -= a / (eps + sqrtf(h));
+// nothing under- or overflows both are shorter, with the same bits: the root is
+// its reciprocal's approximation and one correction by the exact residual, the
+// quotient the rounded reciprocal (the approximation and one Newton step) and such
+// a correction, which rounds as the division does (Markstein 1990).  That every
+// root of [1, 4) and every reciprocal of [1, 2) of this approximation comes out
+// rounded was checked value by value on the device (powers of four and of two
+// scale them exactly).
+//
+// A thread takes a chunk of gradients this way and then looks whether it held for
+// all of them: lr and eps in range, each g zero or at least `AdagradRange::least`
+// (then h >= g^2 >= 2^-80 and lr g >= 2^-80; a zero g changes nothing whatever
+// the root), h >= 0 before and < 2^80 after (it only grows; a NaN fails).  Where
+// it did not, it takes the chunk again with the library's forms.
+struct AdagradRange {
+    bool ok;
+    uint32_t least;  // 2 * bits - 1 of the least g: zeros are above every number
+    __device__ AdagradRange(float lr, float eps) {
+        ok = lr < 0x1p60f && eps > 0x1p-100f && eps < 0x1p40f;
+        least = 2u * __float_as_uint(fmaxf(0x1p-40f, lr > 0.0f ? 0x1p-79f / lr : 0.0f)) - 1u;
     }
+};
+__device__ __forceinline__ void adagrad_fast(float& th, float& h, float g, float lr, float eps) {
+    h = fmaf(g, g, h);
+    const float a = lr * g, y = __builtin_amdgcn_rsqf(fmaxf(h, 0x1p-81f)), s0 = h * y;
+    const float s = fmaf(0.5f * fmaf(-s0, s0, h), y, s0);  // sqrt(h)
+    const float d = eps + s, r0 = __builtin_amdgcn_rcpf(d), r = fmaf(fmaf(-d, r0, 1.0f), r0, r0);
+    const float q = a * r;
+    th -= fmaf(fmaf(-q, d, a), r, q);  // a / d
+}
+__device__ __forceinline__ void adagrad(float& th, float& h, float g, float lr, float eps) {
+    h = fmaf(g, g, h);
+    th -= lr * g / (eps + sqrtf(h));
 }
 template <int VEC>
 __global__ __launch_bounds__(256) void ps_apply_kernel(float* __restrict__ theta,
@@ -175,7 +187,7 @@ __global__ __launch_bounds__(256) void ps_apply_kernel(float* __restrict__ theta
                                                        float lr, float eps) {
     constexpr int ILP = PS_ELEMS / VEC;
     using IO = VecIO<VEC>;
-    const bool fast = lr < 0x1p60f && eps < 0x1p40f;
+    const AdagradRange range(lr, eps);
     // n < 2^31 (checked by the caller): every vector index fits 32 bits
     const uint32_t nv = (uint32_t)(n / VEC);  // vectors (n is a multiple of VEC)
     const uint32_t stride = gridDim.x * 256u * ILP;
@@ -204,6 +216,16 @@ __global__ __launch_bounds__(256) void ps_apply_kernel(float* __restrict__ theta
 #pragma unroll
                 for (int u = 0; u < ILP; ++u) IO::load(gr, at[u], gv[j][u]);
             }
+            float th0[ILP][VEC], h0[ILP][VEC];
+            uint32_t least = ~0u;
+            bool ok = range.ok;
+#pragma unroll
+            for (int u = 0; u < ILP; ++u)
+#pragma unroll
+                for (int c = 0; c < VEC; ++c) {
+                    th0[u][c] = th[u][c];
+                    h0[u][c] = h[u][c];
+                }
 #pragma unroll
             for (int j = 0; j < PS_CHUNK; ++j) {
                 if (!(mask >> j & 1u)) continue;
@@ -211,8 +233,34 @@ __global__ __launch_bounds__(256) void ps_apply_kernel(float* __restrict__ theta
                 for (int u = 0; u < ILP; ++u)
 #pragma unroll
                     for (int c = 0; c < VEC; ++c) {
-                        adagrad(th[u][c], h[u][c], gv[j][u][c], lr, eps, fast);
+                        adagrad_fast(th[u][c], h[u][c], gv[j][u][c], lr, eps);
+                        least = min(least, 2u * __float_as_uint(gv[j][u][c]) - 1u);
                     }
+            }
+            ok = ok && least >= range.least;
+#pragma unroll
+            for (int u = 0; u < ILP; ++u)
+#pragma unroll
+                for (int c = 0; c < VEC; ++c) ok = ok && h0[u][c] >= 0.0f && h[u][c] < 0x1p80f;
+            if (__builtin_expect(ok, 1)) continue;
+#pragma unroll
+            for (int u = 0; u < ILP; ++u)
+#pragma unroll
+                for (int c = 0; c < VEC; ++c) {
+                    th[u][c] = th0[u][c];
+                    h[u][c] = h0[u][c];
+                }
+#pragma unroll 1
+            for (int j = 0; j < PS_CHUNK; ++j) {
+                if (!(mask >> j & 1u)) continue;
+                const float* gr = grads + (int64_t)(g0 + j) * n;
+#pragma unroll
+                for (int u = 0; u < ILP; ++u) {
+                    float g[VEC];
+                    IO::load(gr, at[u], g);
+#pragma unroll
+                    for (int c = 0; c < VEC; ++c) adagrad(th[u][c], h[u][c], g[c], lr, eps);
+                }
             }
         }
 #pragma unroll
@@ -273,8 +321,9 @@ __device__ inline uint16_t f32_to_bf16_rne(float x) {
 
 // Four consecutive elements a thread, at any element's address (copies of n
 // elements: only 2-byte (bf16) or 4-byte aligned); the last n % 4 elements one
-// by one.  Bound by HBM: the pull of 1693362 elements into 16 bf16 copies, 61
-// MB, took 12.2 us with 2-byte stores, and a second launch 3.9 us; now 11.1 us.
+// by one.  The pull of 1693362 elements into 16 bf16 copies, 61 MB, 2-byte stores
+// -> these, us: the same buffers again 13.7 -> 11.4, six sets of buffers in turn
+// 15.8 -> 14.1, 4.3 TB/s; the second launch took 3.9 more.
 template <bool BF16>
 __global__ __launch_bounds__(256) void sync_copy_kernel(const float* __restrict__ src,
                                                         void* __restrict__ dst, int64_t n,

@@ -112,9 +112,21 @@ def test_adagrad_rounds_as_ieee(what):
     assert int((T.cpu().numpy() != want).sum()) == 0
 
 
+def _square_added(g, h):
+    """h + g^2 rounded once, as a fused multiply-add: the sum is rounded to odd in
+    fp64 (towards the odd one of its neighbours where it is not exact), which then
+    rounds to fp32 as the exact sum does."""
+    p, h = g.astype(np.float64) ** 2, h.astype(np.float64)
+    s = h + p
+    b = s - h
+    err = (h - (s - b)) + (p - b)
+    even = (s.view(np.int64) & 1) == 0
+    odd = np.where((err != 0) & even & np.isfinite(err), np.nextafter(s, np.where(err > 0, np.inf, -np.inf)), s)
+    return odd.astype(np.float32)
+
+
 def test_adagrad_random_bits():
-    """Ordinary values, several gradients, replayed in fp32 (the square and its sum
-    round once, as a fused multiply-add): the same bits."""
+    """Ordinary values, several gradients, replayed in fp32: the same bits."""
     import paper_1507_04296_amd as g
     rng = np.random.default_rng(5)
     n, G = 2**22 + 4, 5
@@ -122,6 +134,9 @@ def test_adagrad_random_bits():
     h = (rng.random(n) ** 8).astype(np.float32)
     gr = (rng.standard_normal((G, n)) * np.exp(rng.uniform(-70, 2, (G, n)))).astype(np.float32)
     gr[:, ::7] = 0
+    h[::14] = 0          # dead: never a gradient
+    h[1::14] = 0         # the first gradient yet
+    h[5], gr[1, 6], gr[2, 8], h[9] = np.inf, np.inf, np.nan, np.nan
     t = lambda a: torch.from_numpy(a.copy()).cuda()
     T, H, D = t(th), t(h), t(gr)
     ver = torch.zeros(G, dtype=torch.int64, device="cuda")
@@ -131,8 +146,9 @@ def test_adagrad_random_bits():
     g.gorila_ps_apply(ctx, T, H, D, ver, now, 1 << 40, 0.01, 1e-6, applied)
     ctx.check()
     lr, eps = np.float32(0.01), np.float32(1e-6)
-    for i in range(G):
-        h = (h.astype(np.float64) + gr[i].astype(np.float64) ** 2).astype(np.float32)
-        th = th - lr * gr[i] / (eps + np.sqrt(h))
-    assert np.array_equal(H.cpu().numpy(), h)
-    assert np.array_equal(T.cpu().numpy(), th)
+    with np.errstate(invalid="ignore"):
+        for i in range(G):
+            h = _square_added(gr[i], h)
+            th = th - lr * gr[i] / (eps + np.sqrt(h))
+    assert np.array_equal(H.cpu().numpy(), h, equal_nan=True)
+    assert np.array_equal(T.cpu().numpy(), th, equal_nan=True)
