@@ -60,27 +60,6 @@ __device__ __forceinline__ int opaque(int v) {
     return v;
 }
 
-// One reduction step of 32 for NC row tiles (operand a) and NT column tiles
-// (operand b): the leading products into hi, the others into lo.
-template <int PA, int PB, int NC, int NT>
-__device__ __forceinline__ void step_products(const bf16x8 (&a)[NC][PA], const bf16x8 (&b)[NT][PB],
-                                              f32x4 (&hi)[NC][NT], f32x4 (&lo)[NC][NT]) {
-#pragma unroll
-    for (int order = 0; order <= 2; ++order)
-#pragma unroll
-        for (int pa = 0; pa < PA; ++pa) {
-            const int pb = order - pa;
-            if (pb < 0 || pb >= PB) continue;
-#pragma unroll
-            for (int i = 0; i < NC; ++i)
-#pragma unroll
-                for (int j = 0; j < NT; ++j) {
-                    if (order == 0) hi[i][j] = mfma16(a[i][pa], b[j][pb], hi[i][j]);
-                    else lo[i][j] = mfma16(a[i][pa], b[j][pb], lo[i][j]);
-                }
-        }
-}
-
 // Quads of fp32 values or of bf16 bit patterns (widened exactly; stored rounded).
 __device__ inline f32x4 ldq(const float* p) { return ld4(p); }
 __device__ inline f32x4 ldq(const uint16_t* p) {
@@ -115,22 +94,22 @@ __device__ inline f32x4 ldqa(const uint16_t* p) {
                  __uint_as_float((uint32_t)v[2] << 16), __uint_as_float((uint32_t)v[3] << 16)};
 }
 
-// Products of R row tiles with the column tiles J0 .. J0 + C - 1: the leading
-// ones into hi, the others into lo.  Each plane pair is a round of R C
-// independent instructions; the scheduling barriers keep the rounds apart (the
-// compiler would run one accumulator's chain back to back, each waiting for
-// the one before) and let everything but matrix instructions pass.
-template <int J0, int P, int R, int C, int N>
-__device__ __forceinline__ void plane_products(const bf16x8 (&a)[R][P], const bf16x8 (&x)[C][P],
+// One reduction step of 32: products of R row tiles with the column tiles J0 ..
+// J0 + C - 1, the leading ones into hi, the others into lo.  Each plane pair is a
+// round of R C independent instructions; the scheduling barriers (APART) keep the
+// rounds apart, where the compiler would run one accumulator's chain back to back,
+// each waiting for the one before, and let everything but matrix instructions pass.
+template <int J0, bool APART = true, int PA, int PX, int R, int C, int N>
+__device__ __forceinline__ void plane_products(const bf16x8 (&a)[R][PA], const bf16x8 (&x)[C][PX],
                                                f32x4 (&hi)[R][N], f32x4 (&lo)[R][N]) {
     auto round = [&](auto pc, auto qc, f32x4 (&acc)[R][N]) {
         constexpr int pa = decltype(pc)::value, px = decltype(qc)::value;
-        if constexpr (pa < P && px < P) {
+        if constexpr (pa < PA && px < PX) {
 #pragma unroll
             for (int i = 0; i < R; ++i)
 #pragma unroll
                 for (int j = 0; j < C; ++j) acc[i][J0 + j] = mfma16(a[i][pa], x[j][px], acc[i][J0 + j]);
-            __builtin_amdgcn_sched_barrier(0x7f6);
+            if constexpr (APART) __builtin_amdgcn_sched_barrier(0x7f6);
         }
     };
     constexpr std::integral_constant<int, 0> I0{};

@@ -265,7 +265,7 @@ __global__ __launch_bounds__(TR_THREADS) void trunk_fwd_kernel(
 #pragma unroll
             for (int s = 0; s < 8; ++s) {
                 if (s + 1 < 8) xload(s + 1);
-                step_products(w[s & 1], x[s & 1], hi, lo);
+                plane_products<0, false>(w[s & 1], x[s & 1], hi, lo);
                 if (s + 2 < 8) wload(wf2, 4, 2, s + 2);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -331,7 +331,7 @@ __global__ __launch_bounds__(TR_THREADS) void trunk_fwd_kernel(
 #pragma unroll
             for (int s = 0; s < 9; ++s) {
                 if (s + 1 < 9) xload(s + 1);
-                step_products(w[s & 1], x[s & 1], hi, lo);
+                plane_products<0, false>(w[s & 1], x[s & 1], hi, lo);
                 if (s + 2 < 9) wload(wf3, 4, 2, s + 2);
                 // the next sample's frames come from memory: requested behind
                 // this sample's last weights, they are waited for by no one
